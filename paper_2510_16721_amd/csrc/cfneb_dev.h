@@ -9,10 +9,12 @@
 //                               image's cell, wrapped to [0, 1), as 32-bit fixed point
 //   F      [slot][3][ld]  T     Cartesian forces (T = float, or double for FP64 bands)
 //   FN     [slot][3][ld]  FP64  NEB force (only when recording is on)
-//   binfo  [slot][N]      int4  (bin, rank in bin, packed lattice image) per atom
-//   bins   [slot][...]    int   counts, starts; bpos: atoms in bin order (R, packed id)
+//   binfo  [slot][3][N]   int   bin, rank in bin, packed lattice image of each atom
+//   bins   [slot][...]    int   counts, starts; bpos: atoms in bin order (BinAtom)
 //   nbr    [slot][cap][N] u32   packed neighbour entries, entry-major (readouts only)
-//   cand   [slot][ccap][N] u32  candidates within rc + skin (atom index and shifts)
+//   cand   [slot][N / 64][ccap / 4][64][4] u32  candidates within rc + skin (atom index
+//                               and shifts): four entries of an atom are one 16-byte
+//                               access, 64 atoms' fours are contiguous
 //   ncnt   [slot][N]      int   neighbour count (may exceed cap: overflow)
 //   dvec   [slot][cap][N] T4    Tersoff: bond vector and length (bonds past the fourth)
 //   bo     [slot][cap][N] T2    Tersoff: b_ij and db/dzeta (same)
@@ -34,6 +36,11 @@
 
 #define CFNEB_MAX_IMAGES 64
 #define CFNEB_TILE 256           // threads per block of every streaming kernel
+// Atoms per item of the candidate scan: in a dense system about ten groups of bins, two
+// or three a wave, so that bands of a few 10^5 atom-images still give every SIMD several
+// waves (LJ, 11 images of 16,383 atoms: 251 us with items of 256 bins, 148 us with 96
+// atoms; 22 images of 97,555: 821 us with 192 atoms, 923 us with 96).
+#define CFNEB_TILE_CAND 128
 #define CFNEB_TILE4 1024         // rows (atoms) of a streaming item with 4 per thread
 #define CFNEB_WAVES 4            // waves per block of CFNEB_TILE threads
 #define CFNEB_NDOT 22            // band-dot partial sums per moving image and row tile
@@ -54,11 +61,12 @@
 
 namespace cfneb {
 
-// One atom in bin order: unwrapped position and (id, lattice image) packed as
-// id | (n0 + 512) << 20 | (n1 + 512) << 30 | (n2 + 512) << 40.
-struct alignas(32) BinAtom {
-    double x, y, z;
-    long long info;
+// One atom in bin order: position wrapped into the cell, rounded to FP32, and its id
+// (low 20 bits) with the negated lattice image of the unwrapped position, 4 bits per
+// axis modulo 16 (exact while SkinState::far is 0).
+struct alignas(16) BinAtom {
+    float x, y, z;
+    uint32_t code;
 };
 
 struct ImageGeom {
@@ -90,6 +98,7 @@ struct SkinState {
     int valid;                 // a candidate list exists for this slot
     int rebuild;               // this step rebuilds it
     int held;                  // rebuild, set aside while the force grid is tuned
+    int far;                   // an atom lay more than 3 cells away at the last build
 };
 
 struct ImageScal {
@@ -161,13 +170,13 @@ struct BandDev {
     uint32_t* S;        // FP32 LJ bands, else null: three words per atom
     void* F;
     double* FN;
-    int4* binfo;
+    int* binfo;         // [slot][3][N]
     int* bcount;
     int* bstart;
     struct BinAtom* bpos;
     uint32_t* nbr;
     int* ncnt;
-    uint32_t* cand;     // [slot][ccap][N] candidate entries, packed like nbr
+    uint32_t* cand;     // [slot][cand_words] candidate entries, packed like nbr (cand_at)
     int* ncand;         // [slot][N]
     float* Rref;        // [slot][3][ld] positions at the candidate build, rounded to FP32
     SkinState* skst;    // [slot]
@@ -293,6 +302,15 @@ __device__ inline double* Vs(const BandDev& b, int buf, int slot)
 __device__ inline R3* Rs(const BandDev& b, int slot) { return reinterpret_cast<R3*>(b.R) + size_t(slot) * b.ld; }
 __device__ inline uint32_t* Ss(const BandDev& b, int slot) { return b.S + size_t(slot) * b.ld * 3; }
 
+// Candidate c of atom i in an image's candidate block: 64 atoms take cand_block words.
+__host__ __device__ inline size_t cand_block(int ccap) { return size_t((ccap + 3) >> 2) * 256; }
+__host__ __device__ inline size_t cand_words(const BandDev& b) { return size_t((b.N + 63) >> 6) * cand_block(b.ccap); }
+__device__ inline uint32_t* Cs(const BandDev& b, int slot) { return b.cand + size_t(slot) * cand_words(b); }
+__device__ inline size_t cand_at(int ccap, int i, int c)
+{
+    return size_t(i >> 6) * cand_block(ccap) + size_t(c >> 2) * 256 + (i & 63) * 4 + (c & 3);
+}
+
 __device__ inline uint32_t pack_nbr(int j, int n0, int n1, int n2)
 {
     return uint32_t(j) | (uint32_t(n0 + 8) << 20) | (uint32_t(n1 + 8) << 24) | (uint32_t(n2 + 8) << 28);
@@ -349,6 +367,7 @@ enum ItemKind {
     KIND_BAND,      // one item per band
     KIND_ATOM4,     // 1024-atom tiles x images (4 atoms per thread)
     KIND_ROW4,      // 1024-row tiles x images (4 rows per thread)
+    KIND_CAND,      // shares of the candidate scan's bin groups x images
     NKIND
 };
 
@@ -380,6 +399,7 @@ __device__ inline int kind_tiles(const BandDev& b, int kind)
     case KIND_ATOM: return b.ntA;
     case KIND_ATOM4: return (b.N + CFNEB_TILE4 - 1) / CFNEB_TILE4;
     case KIND_ROW4: return b.ntR4;
+    case KIND_CAND: return (b.N + CFNEB_TILE_CAND - 1) / CFNEB_TILE_CAND;
     case KIND_BIN: return (b.nbcap + CFNEB_TILE - 1) / CFNEB_TILE;
     case KIND_ROW:
     case KIND_IVAL:

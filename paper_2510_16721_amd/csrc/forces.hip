@@ -23,7 +23,7 @@ namespace cfneb {
 // Lennard-Jones straight from the candidates (Verlet skin): each candidate gets the
 // exact inclusion test and, if it is a neighbour, its pair term, so neither a packed
 // neighbour list nor a second gather of the positions is needed in a step.  K lanes
-// share an atom, taking candidates l, l + K, l + 2K, ... (lane l); the atom's force
+// share an atom, taking fours of candidates l, l + K, l + 2K, ... (lane l); the atom's force
 // is the fixed butterfly sum of its lanes, energy and virial go into the wave sums.
 // A tile of 256 atoms is covered in K passes of 256 / K atoms.
 //
@@ -72,7 +72,7 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
     const size_t N = b.N;
     const int lane = int(threadIdx.x) % K;
     const gmem<const R3>* __restrict__ R = gp<const R3>(Rs(b, slot));
-    const gmem<const uint32_t>* __restrict__ cand = gp<const uint32_t>(b.cand + size_t(slot) * b.ccap * N);
+    const gmem<const uint4>* __restrict__ cand = gp<const uint4>(reinterpret_cast<const uint4*>(Cs(b, slot)));
     const gmem<const int>* __restrict__ ncand = gp<const int>(b.ncand + size_t(slot) * N);
     gmem<T>* F = gp(reinterpret_cast<T*>(b.F) + size_t(slot) * slot_rows(b));
     const cmem<ImageGeom>* g = cp(b.geom + slot);
@@ -93,24 +93,21 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
         const int nc = in ? ncand[ii] : 0;
         T fx = 0, fy = 0, fz = 0;
         int cnt = 0;
-        // four of the lane's candidates at a time: entries, then positions, in flight
-        // together (past the last candidate the loads repeat it; the tests stop there)
+        // four consecutive candidates at a time (one 16-byte load), their positions in
+        // flight together (entries past the last candidate hold atoms of an earlier list
+        // or atom 0: in bounds; the tests stop there)
         constexpr int U = 4;
-        for (int e0 = lane; e0 < nc; e0 += U * K) {
-            uint32_t ent[U];
+        for (int e0 = U * lane; e0 < nc; e0 += U * K) {
+            const uint4 four = load4(cand, cand_at(b.ccap, i, e0) >> 2);
+            const uint32_t ent[U] = {four.x, four.y, four.z, four.w};
             double4 rj[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int c = e0 + u * K;
-                ent[u] = cand[size_t(c < nc ? c : e0) * N + ii];
-            }
 #pragma unroll
             for (int u = 0; u < U; ++u) rj[u] = load4(R, nbr_j(ent[u]));
             __builtin_amdgcn_sched_barrier(0);
             T w[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (e0 + u * K >= nc) break;
+                if (e0 + u >= nc) break;
                 double d[3];
                 separation(ri, rj[u], h, ent[u], d);
                 const T dx = T(d[0]), dy = T(d[1]), dz = T(d[2]);
@@ -170,9 +167,9 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
 // The FP32 r^2 settles the pair outside [r2lo, r2hi); inside that band the exact FP64
 // test runs on the FP64 positions.
 // Loads at a 32-bit byte offset from a uniform base (one address add per load).
-__device__ inline uint32_t ld_u32(const void* base, uint32_t off)
+__device__ inline uint4 ld_u128(const void* base, uint32_t off)
 {
-    return *reinterpret_cast<const gmem<const uint32_t>*>(gp(static_cast<const char*>(base)) + off);
+    return load4(reinterpret_cast<const gmem<const uint4>*>(gp(static_cast<const char*>(base)) + off), 0);
 }
 __device__ inline uint4 ld_u96(const void* base, uint32_t off)
 {
@@ -184,12 +181,11 @@ template <int K>
 __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int tile)
 {
     // band fields as uniform locals: read once, held in scalar registers
-    const int Ni = uni(b.N), ld = uni(b.ld), cap = uni(b.cap);
-    const uint32_t N = uint32_t(Ni);
+    const int Ni = uni(b.N), ld = uni(b.ld), cap = uni(b.cap), ccap = uni(b.ccap);
     const int lane = int(threadIdx.x) % K;
     const uint32_t* S = uni(Ss(b, slot));
-    const uint32_t* cand = uni(b.cand + size_t(slot) * b.ccap * N);
-    const gmem<const int>* __restrict__ ncand = gp<const int>(uni(b.ncand + size_t(slot) * N));
+    const uint32_t* cand = uni(Cs(b, slot));
+    const gmem<const int>* __restrict__ ncand = gp<const int>(uni(b.ncand + size_t(slot) * Ni));
     gmem<float>* F = gp(uni(reinterpret_cast<float*>(b.F) + size_t(slot) * slot_rows(b)));
     const gmem<const R3>* R = gp<const R3>(uni(Rs(b, slot)));
     const cmem<ImageGeom>* g = cp(b.geom + slot);
@@ -214,22 +210,17 @@ __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int til
         const int nc = in ? ncand[ii] : 0;
         float fx = 0.f, fy = 0.f, fz = 0.f;
         int cnt = 0;
-        // four of the lane's candidates at a time, loads first; past the last candidate
-        // the loads repeat the batch's first and the pair is masked out
+        // four consecutive candidates at a time (one 16-byte load), their positions in
+        // flight together; entries past the last candidate hold atoms of an earlier list
+        // or atom 0 (in bounds) and their pairs are masked out
         constexpr int U = 4;
-        // candidate c = base + u K + lane of this atom sits at byte (c N + i) 4: a uniform
-        // row offset plus this lane's constant (no per-candidate multiply)
-        const uint32_t own = (uint32_t(lane) * N + ii) * 4u, row = N * 4u;
-        for (int base = 0; base + lane < nc; base += U * K) {
-            const int e0 = base + lane;
-            uint32_t ent[U];
+        // the wave's atoms share one block of 64: a uniform base and a 32-bit offset
+        const uint32_t* block = uni(cand + size_t(i >> 6) * cand_block(ccap));
+        uint32_t off = (uint32_t(lane) * 64u + uint32_t(i & 63)) * 16u;
+        for (int e0 = U * lane; e0 < nc; e0 += U * K, off += uint32_t(K) * 1024u) {
+            const uint4 four = ld_u128(block, off);
+            const uint32_t ent[U] = {four.x, four.y, four.z, four.w};
             uint4 sj[U];
-            const uint32_t o0 = uint32_t(base) * row + own;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t o = o0 + uint32_t(u * K) * row;
-                ent[u] = ld_u32(cand, e0 + u * K < nc ? o : o0);
-            }
 #pragma unroll
             for (int u = 0; u < U; ++u) sj[u] = ld_u96(S, uint32_t(nbr_j(ent[u])) * 12u);
             __builtin_amdgcn_sched_barrier(0);
@@ -244,7 +235,7 @@ __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int til
                 const float dy = float(a0 * H[1] + a1 * H[4] + a2 * H[7]);
                 const float dz = float(a0 * H[2] + a1 * H[5] + a2 * H[8]);
                 const float r2 = dx * dx + dy * dy + dz * dz;
-                const bool valid = e0 + u * K < nc;
+                const bool valid = e0 + u < nc;
                 bool inside = valid && r2 < lo;
                 if (valid && r2 >= lo && r2 < hi) {  // rare: the exact FP64 test on the FP64 positions
                     const double4 r4 = load4(R, ii);

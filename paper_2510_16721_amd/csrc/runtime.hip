@@ -67,13 +67,13 @@ bool make_layout(const cfneb_params* p, int64_t n_atoms, int max_images, Layout*
     L->S = take(L->tersoff || L->fp64 ? 0 : M * size_t(L->ld) * 12);
     L->F = take(M * rows * tsz);
     L->FN = take(M * rows * 8);
-    L->binfo = take(M * N * 16);
+    L->binfo = take(M * N * 12);
     L->bcount = take(M * (L->nbcap + 1) * 4);
     L->bstart = take(M * (L->nbcap + 1) * 4);
     L->bpos = take(M * N * sizeof(BinAtom));
     L->nbr = take(M * size_t(L->cap) * N * 4);
     L->ncnt = take(M * N * 4);
-    L->cand = take(M * size_t(L->ccap) * N * 4);
+    L->cand = take(M * size_t((L->ccap + 3) / 4) * ((N + 63) / 64) * 1024);
     L->ncand = take(M * N * 4);
     L->Rref = take(M * rows * 4);
     L->skin = take(M * sizeof(SkinState));
@@ -125,6 +125,7 @@ void size_grids(Launch& L, long long atom_tiles, long long row_tiles, long long 
     L.g[KIND_ATOM] = grid_for(atom_tiles, CFNEB_GRID_TILES);
     L.g[KIND_ROW] = grid_for(row_tiles, CFNEB_GRID_TILES);
     L.g[KIND_BIN] = grid_for(bin_tiles, CFNEB_GRID_TILES);
+    L.g[KIND_CAND] = grid_for(2 * atom_tiles, CFNEB_GRID_TILES);  // tiles of 128 atoms
     L.g[KIND_IMAGE] = grid_for(images, CFNEB_GRID_IMAGES);
     L.g[KIND_IVAL] = grid_for(row_tiles, CFNEB_GRID_TILES);
     L.g[KIND_SLOTROW] = grid_for(row_tiles, CFNEB_GRID_TILES);
@@ -304,7 +305,7 @@ void fill_dev(cfneb_band* b, void* ws, const double* h0, int relax)
     d.S = (L.tersoff || d.fp64) ? nullptr : reinterpret_cast<uint32_t*>(base + L.S);
     d.F = base + L.F;
     d.FN = reinterpret_cast<double*>(base + L.FN);
-    d.binfo = reinterpret_cast<int4*>(base + L.binfo);
+    d.binfo = reinterpret_cast<int*>(base + L.binfo);
     d.bcount = reinterpret_cast<int*>(base + L.bcount);
     d.bstart = reinterpret_cast<int*>(base + L.bstart);
     d.bpos = reinterpret_cast<BinAtom*>(base + L.bpos);

@@ -380,21 +380,24 @@ __device__ void ts_atom_generic(const TersoffT<T>& P, const vec4_t<T>* dv, vec2_
 __device__ void ts_reverse_candidates(const BandDev& b, BandState* st, int slot, int i, int nc)
 {
     const size_t N = b.N;
-    const gmem<const uint32_t>* __restrict__ cand = gp<const uint32_t>(b.cand + size_t(slot) * b.ccap * N);
+    const gmem<const uint4>* __restrict__ cand4 = gp<const uint4>(reinterpret_cast<const uint4*>(Cs(b, slot)));
+    const gmem<const uint32_t>* __restrict__ cand = gp<const uint32_t>(Cs(b, slot));
     const gmem<const int>* __restrict__ ncand = gp<const int>(b.ncand + size_t(slot) * N);
     gmem<uint32_t>* __restrict__ crev = gp(b.crev + size_t(slot) * b.ccap * N);
     bool missing = false;
     for (int c = 0; c < nc; ++c) {
-        const uint32_t ent = cand[size_t(c) * N + i];
+        const uint32_t ent = cand[cand_at(b.ccap, i, c)];
         const int j = nbr_j(ent);
         const uint32_t want = pack_nbr(i, -nbr_n(ent, 0), -nbr_n(ent, 1), -nbr_n(ent, 2));
         const int cj = ncand[j];
         int found = -1;
-        for (int q = 0; q < cj; ++q)
-            if (cand[size_t(q) * N + j] == want) {
-                found = q;
-                break;
-            }
+        for (int q = 0; q < cj && found < 0; q += 4) {
+            const uint4 e = load4(cand4, cand_at(b.ccap, j, q) >> 2);
+            const uint32_t ee[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+            for (int u = 3; u >= 0; --u)
+                if (ee[u] == want && q + u < cj) found = q + u;
+        }
         if (found < 0) {
             missing = true;
             found = 0;
@@ -425,7 +428,7 @@ __device__ void ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
     if (i < b.N) {
         const cmem<ImageGeom>* g = cp(b.geom + slot);
         const gmem<const R3>* __restrict__ R = gp<const R3>(Rs(b, slot));
-        const gmem<const uint32_t>* __restrict__ cand = gp<const uint32_t>(b.cand + size_t(slot) * b.ccap * N);
+        const gmem<const uint4>* __restrict__ cand = gp<const uint4>(reinterpret_cast<const uint4*>(Cs(b, slot)));
         P3<T>* Praw = reinterpret_cast<P3<T>*>(b.P) + size_t(slot) * b.ccap * N;
         gmem<P3<T>>* __restrict__ Pout = gp(Praw);
         vec4_t<T>* dv = reinterpret_cast<vec4_t<T>*>(b.dvec) + size_t(slot) * b.cap * N;
@@ -444,12 +447,11 @@ __device__ void ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
         // dependent loads for most atoms; the tests stop at the atom's last candidate
         constexpr int U = 4;
         for (int e0 = 0; e0 < nc; e0 += U) {
-            uint32_t ent[U];
+            // entries past the last candidate hold atoms of an earlier list or atom 0
+            // (in bounds); the tests below stop there
+            const uint4 e4 = load4(cand, cand_at(b.ccap, i, e0) >> 2);
+            const uint32_t ent[U] = {e4.x, e4.y, e4.z, e4.w};
             double4 rj[U];
-            // past the last candidate the loads repeat it (in bounds, no branch
-            // between the loads); the tests below stop there
-#pragma unroll
-            for (int u = 0; u < U; ++u) ent[u] = cand[size_t(min(e0 + u, nc - 1)) * N + i];
 #pragma unroll
             for (int u = 0; u < U; ++u) rj[u] = load4(R, nbr_j(ent[u]));
             __builtin_amdgcn_sched_barrier(0);  // the batch's positions are in flight together
