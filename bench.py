@@ -420,7 +420,7 @@ def throughput(args):
     elif dom == "force0":
         # the LJ candidate kernel (exact test and pair term of every candidate)
         achieved = flops_per_atom * atoms / (kernel_ms * 1e-3) / 1e12
-        roof = dict(bound="alu", kernel="k_lj_cand<float, 1>", achieved=achieved, peak=VALU_FP32_PEAK_TFLOPS,
+        roof = dict(bound="alu", kernel="k_lj_one<float>", achieved=achieved, peak=VALU_FP32_PEAK_TFLOPS,
                     unit="TFLOP/s", frac=achieved / VALU_FP32_PEAK_TFLOPS,
                     traffic=recorded("lj_fcc_vacancy_97555_hbm_counters.md", "force_kernel_hbm_bytes", mean_moving),
                     valu_issue_util=recorded("lj_fcc_vacancy_97555_valu_counters.md", "valu_issue_util"))

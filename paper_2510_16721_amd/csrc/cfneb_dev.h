@@ -145,11 +145,13 @@ struct BandState {
 // Everything a kernel needs, passed by value.
 struct BandDev {
     int N, ld, Mcap, ntA, ntR, ntR4, nbcap, cap, ccap;
+    int ntF;       // items of the force kernel that forms energies, per image
+    int lj_tile;   // atoms of such an item in the LJ kernel (256 / lj_lanes where it fits)
     int potential, fp64;
     double rc, rc2;
     double skin, rcl, rcl2;  // candidate skin, list cutoff rc + skin and its square
     double lj_eps, lj_sig2, lj_eshift;
-    int lj_lanes;  // lanes sharing an atom in the LJ force kernel (1, 2, 4 or 8)
+    int lj_lanes;  // lanes sharing an atom in the LJ force kernel (1, 2, 4, 8, 16 or 32)
     double ts_A, ts_B, ts_l1, ts_l2, ts_beta, ts_bn, ts_lnbeta, ts_n, ts_c2, ts_d2, ts_c2d2, ts_h, ts_R, ts_S;
     double k_spring;
     int climb_after, cell_filter;
@@ -191,7 +193,7 @@ struct BandDev {
     uint32_t* crev;
     ImageGeom* geom;
     ImageScal* scal;
-    double* evpart;     // [slot][ntA][4][10]: energy and virial sums of each wave of a tile
+    double* evpart;     // [slot][ntF][4][10]: energy and virial sums of each wave of an item
     double* dotpart;    // [k][CFNEB_NDOT][ntR4][4]: one partial per wave of each 1024-row item
     double* dotred;     // [k][CFNEB_NDOT] reduced band dots
     double* maxpart;    // [k][3][ntR4]
@@ -367,6 +369,12 @@ enum ItemKind {
     KIND_BAND,      // one item per band
     KIND_ATOM4,     // 1024-atom tiles x images (4 atoms per thread)
     KIND_ROW4,      // 1024-row tiles x images (4 rows per thread)
+    // items of the energy-forming force kernels (ntF) x images, each kind holding only
+    // the bands that its kernel serves (a kernel that walks the items of other bands to
+    // skip them pays a chain of scalar loads for each: 15 us a step on a mix of 64 bands)
+    KIND_LJ1,       // LJ bands of one lane per atom
+    KIND_LJK,       // LJ bands of several
+    KIND_TS,        // Tersoff bands (also the gather)
     KIND_CAND,      // shares of the candidate scan's bin groups x images
     NKIND
 };
@@ -399,6 +407,9 @@ __device__ inline int kind_tiles(const BandDev& b, int kind)
     case KIND_ATOM: return b.ntA;
     case KIND_ATOM4: return (b.N + CFNEB_TILE4 - 1) / CFNEB_TILE4;
     case KIND_ROW4: return b.ntR4;
+    case KIND_LJ1: return b.potential == CFNEB_LJ && b.lj_lanes == 1 ? b.ntF : 0;
+    case KIND_LJK: return b.potential == CFNEB_LJ && b.lj_lanes > 1 ? b.ntF : 0;
+    case KIND_TS: return b.potential == CFNEB_TERSOFF_C ? b.ntF : 0;
     case KIND_CAND: return (b.N + CFNEB_TILE_CAND - 1) / CFNEB_TILE_CAND;
     case KIND_BIN: return (b.nbcap + CFNEB_TILE - 1) / CFNEB_TILE;
     case KIND_ROW:
@@ -552,14 +563,13 @@ __host__ __device__ inline int band_variant(const BandDev& b)
     return (b.potential == CFNEB_TERSOFF_C ? 2 : 0) + (b.fp64 ? 1 : 0);
 }
 
-// Bits 8..11 of a launch's variant set: the LJ lane counts 1, 2, 4, 8 present (each
-// band keeps its own count, alone and in a batch, so its sums never depend on its
-// batch-mates).
+// Bits 8 and 9 of a launch's variant set: LJ bands with one lane per atom, and with
+// several, present (each band keeps its own count, alone and in a batch, so its sums
+// never depend on its batch-mates).
 __host__ __device__ inline unsigned lanes_bit(const BandDev& b)
 {
     if (b.potential != CFNEB_LJ) return 0u;
-    const int k = b.lj_lanes;
-    return 1u << (8 + (k >= 8 ? 3 : k >= 4 ? 2 : k >= 2 ? 1 : 0));
+    return b.lj_lanes == 1 ? 1u << 8 : 1u << 9;
 }
 __host__ __device__ inline unsigned launch_variants(const BandDev& b) { return (1u << band_variant(b)) | lanes_bit(b); }
 
@@ -615,6 +625,49 @@ __device__ inline double dpp_f64(double x)
     const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(0, int(unsigned(v)), CTRL, 0xF, 0xF, true));
     const unsigned hi = unsigned(__builtin_amdgcn_update_dpp(0, int(unsigned(v >> 32)), CTRL, 0xF, 0xF, true));
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <int CTRL>
+__device__ inline int dpp_i32(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
+}
+// Sum over K consecutive lanes (aligned, K a power of two up to 32), the same value in
+// each of them: partners lane ^ 1, ^ 2, then mirrored within 8 and 16, then 16 apart.
+template <int K>
+__device__ inline float lanes_sum(float v)
+{
+    if constexpr (K > 1) v += __int_as_float(dpp_i32<0xB1>(__float_as_int(v)));
+    if constexpr (K > 2) v += __int_as_float(dpp_i32<0x4E>(__float_as_int(v)));
+    if constexpr (K > 4) v += __int_as_float(dpp_i32<0x141>(__float_as_int(v)));
+    if constexpr (K > 8) v += __int_as_float(dpp_i32<0x140>(__float_as_int(v)));
+    if constexpr (K > 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+    return v;
+}
+template <int K>
+__device__ inline int lanes_sum(int v)
+{
+    if constexpr (K > 1) v += dpp_i32<0xB1>(v);
+    if constexpr (K > 2) v += dpp_i32<0x4E>(v);
+    if constexpr (K > 4) v += dpp_i32<0x141>(v);
+    if constexpr (K > 8) v += dpp_i32<0x140>(v);
+    if constexpr (K > 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(unsigned(v), unsigned(v), false, false);
+        v = int(s[0]) + int(s[1]);
+    }
+    return v;
+}
+template <int K>
+__device__ inline double lanes_sum(double v)
+{
+    if constexpr (K > 1) v += dpp_f64<0xB1>(v);
+    if constexpr (K > 2) v += dpp_f64<0x4E>(v);
+    if constexpr (K > 4) v += dpp_f64<0x141>(v);
+    if constexpr (K > 8) v += dpp_f64<0x140>(v);
+    if constexpr (K > 16) v = swap_add<false>(v, v);
+    return v;
 }
 // Sum and maximum over a wave, the same value in every lane: partners 32 and 16
 // lanes apart through the lane swaps, then lane ^ 15, ^ 7, ^ 2 and ^ 1 within a row
@@ -872,7 +925,7 @@ __device__ inline void tersoff_gather(const BandDev& b, int slot, int i0, int st
     }
 }
 
-// Energy and virial partials of one 256-atom tile: each wave stores its own ten sums
+// Energy and virial partials of one item of the force kernel: each wave stores its own ten sums
 // (transposed wave reduction, no block barrier).  Every wave of the tile stores, so
 // no partial of an earlier evaluation survives.
 __device__ inline void store_ev_partials(const BandDev& b, int slot, int tile, const double (&v)[10])
@@ -881,7 +934,7 @@ __device__ inline void store_ev_partials(const BandDev& b, int slot, int tile, c
     constexpr int LOGP = wave_sum_logp<10>();
     const int lane = int(threadIdx.x) & 63, idx = lane >> (6 - LOGP);
     if ((lane & ((64 >> LOGP) - 1)) == 0 && idx < 10)
-        b.evpart[((size_t(slot) * b.ntA + tile) * CFNEB_WAVES + (int(threadIdx.x) >> 6)) * 10 + idx] = s;
+        b.evpart[((size_t(slot) * b.ntF + tile) * CFNEB_WAVES + (int(threadIdx.x) >> 6)) * 10 + idx] = s;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -893,8 +946,8 @@ __device__ inline void store_ev_partials(const BandDev& b, int slot, int tile, c
 __device__ inline void image_reduce_item(const BandDev& b, BandState* st, int slot, double* lds)
 {
     double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    const double* part = b.evpart + size_t(slot) * b.ntA * CFNEB_WAVES * 10;
-    for (int t = threadIdx.x; t < b.ntA * CFNEB_WAVES; t += CFNEB_TILE)
+    const double* part = b.evpart + size_t(slot) * b.ntF * CFNEB_WAVES * 10;
+    for (int t = threadIdx.x; t < b.ntF * CFNEB_WAVES; t += CFNEB_TILE)
         for (int q = 0; q < 10; ++q) acc[q] += part[size_t(t) * 10 + q];
     block_sum<10>(acc, lds);
     if (threadIdx.x != 0) return;

@@ -25,7 +25,9 @@ namespace cfneb {
 // neighbour list nor a second gather of the positions is needed in a step.  K lanes
 // share an atom, taking fours of candidates l, l + K, l + 2K, ... (lane l); the atom's force
 // is the fixed butterfly sum of its lanes, energy and virial go into the wave sums.
-// A tile of 256 atoms is covered in K passes of 256 / K atoms.
+// An item is 256 / K atoms, so more lanes are more blocks: a band of a few thousand
+// atom-images fills the chip (255 atoms, 5 moving images, FP64: 5 blocks of one lane an
+// atom 32.5 us, 8.7 us with 16; lj_lanes_table.h has the times of every size).
 //
 // FP64-record path (FP64 bands, narrow cells): the inclusion test decides on the
 // exact FP64 r^2 (every operation rounded on its own): the separation d is formed in FP64 (a candidate without a lattice shift, most
@@ -84,8 +86,8 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};  // u, then V xx yy zz xy xz yz
     bool over = false, bad = false;
 #pragma unroll 1
-    for (int sub = 0; sub < K; ++sub) {
-        const int i = tile * CFNEB_TILE + sub * (CFNEB_TILE / K) + int(threadIdx.x) / K;
+    for (int a0 = 0; a0 < (K > 1 ? b.lj_tile : CFNEB_TILE); a0 += CFNEB_TILE / K) {
+        const int i = (K > 1 ? tile * b.lj_tile : tile * CFNEB_TILE) + a0 + int(threadIdx.x) / K;
         const bool in = i < b.N;
         const int ii = in ? i : 0;
         const double4 r4 = load4(R, ii);
@@ -136,14 +138,10 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
 #pragma unroll
             for (int q = 0; q < 6; ++q) acc[1 + q] += double(w[q]);
         }
-        // the atom's lanes: fixed butterfly (K consecutive, aligned lanes)
-#pragma unroll
-        for (int off = K / 2; off > 0; off >>= 1) {
-            fx += __shfl_xor(fx, off, 64);
-            fy += __shfl_xor(fy, off, 64);
-            fz += __shfl_xor(fz, off, 64);
-            cnt += __shfl_xor(cnt, off, 64);
-        }
+        fx = lanes_sum<K>(fx);
+        fy = lanes_sum<K>(fy);
+        fz = lanes_sum<K>(fz);
+        cnt = lanes_sum<K>(cnt);
         if (in && lane == 0) {
             F[i] = fx;
             F[b.ld + i] = fy;
@@ -202,8 +200,8 @@ __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int til
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};  // 2 u, then -2 V / (24 eps): xx yy zz xy xz yz
     bool over = false, bad = false;
 #pragma unroll 1
-    for (int sub = 0; sub < K; ++sub) {
-        const int i = tile * CFNEB_TILE + sub * (CFNEB_TILE / K) + int(threadIdx.x) / K;
+    for (int a0 = 0; a0 < (K > 1 ? b.lj_tile : CFNEB_TILE); a0 += CFNEB_TILE / K) {
+        const int i = (K > 1 ? tile * b.lj_tile : tile * CFNEB_TILE) + a0 + int(threadIdx.x) / K;
         const bool in = i < Ni;
         const uint32_t ii = in ? uint32_t(i) : 0u;
         const uint4 si = ld_u96(S, ii * 12u);
@@ -270,13 +268,10 @@ __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int til
 #pragma unroll
             for (int q = 1; q < 7; ++q) acc[q] += double(w[q]);
         }
-#pragma unroll
-        for (int off = K / 2; off > 0; off >>= 1) {
-            fx += __shfl_xor(fx, off, 64);
-            fy += __shfl_xor(fy, off, 64);
-            fz += __shfl_xor(fz, off, 64);
-            cnt += __shfl_xor(cnt, off, 64);
-        }
+        fx = lanes_sum<K>(fx);
+        fy = lanes_sum<K>(fy);
+        fz = lanes_sum<K>(fz);
+        cnt = lanes_sum<K>(cnt);
         if (in && lane == 0) {
             F[i] = eps24 * fx;
             F[ld + i] = eps24 * fy;
@@ -294,51 +289,76 @@ __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int til
 }
 
 template <typename T, int K>
-__device__ void lj_cand_loop(const BatchDev& bd, int all_images, int variant)
+__device__ __forceinline__ void lj_item(const BandDev& b, BandState* st, int slot, int tile)
 {
-    ItemLoopRO loop(bd, KIND_ATOM, all_images);
+    if constexpr (std::is_same<T, float>::value) {
+        if (cp(b.geom + slot)->wrap) {  // uniform over the block
+            lj_fixed_item<K>(b, st, slot, tile);
+            return;
+        }
+    }
+    lj_cand_item<T, K>(b, st, slot, tile);
+}
+
+// Bands of one lane per atom (the large ones).
+template <typename T>
+__device__ void lj_one_loop(const BatchDev& bd, int all_images, int variant)
+{
+    ItemLoopRO loop(bd, KIND_LJ1, all_images);
     Item it;
     while (loop.next(it)) {
         const BandDev b = band_ro(bd, it.band);
-        BandState* st = b.st;
-        const cmem<BandState>* sr = cp(st);
-        if (int(band_variant(b) != variant) | int(b.lj_lanes != K) | int(band_stopped(sr))) continue;  // uniform over the block
-        const int slot = sr->slot[it.image];
-        if constexpr (std::is_same<T, float>::value) {
-            if (cp(b.geom + slot)->wrap) {  // uniform over the block
-                lj_fixed_item<K>(b, st, slot, it.tile);
-                continue;
-            }
-        }
-        lj_cand_item<T, K>(b, st, slot, it.tile);
+        const cmem<BandState>* sr = cp(b.st);
+        if (int(band_variant(b) != variant) | int(band_stopped(sr))) continue;  // uniform over the block
+        lj_item<T, 1>(b, b.st, sr->slot[it.image], it.tile);
     }
 }
 
-template <typename T, int K>
-__global__ void __launch_bounds__(CFNEB_TILE) k_lj_cand(BatchDev bd, int all_images, int variant)
+template <typename T>
+__global__ void __launch_bounds__(CFNEB_TILE) k_lj_one(BatchDev bd, int all_images, int variant)
 {
-    lj_cand_loop<T, K>(bd, all_images, variant);
+    lj_one_loop<T>(bd, all_images, variant);
 }
 
-// FP32, one lane per atom (the large bands): five waves per SIMD at a small spill run
-// faster than four without one (force kernel 391 -> 365 us on the 97,555-atom band);
-// the other variants keep their registers (they spill 20-24 dwords at five).
+// FP32, one lane per atom: five waves per SIMD at a small spill run faster than four
+// without one (force kernel 391 -> 365 us on the 97,555-atom band); with several lanes
+// the kernel keeps its registers (it would spill 20-24 dwords at five).
 template <>
 __global__ void __launch_bounds__(CFNEB_TILE) __attribute__((amdgpu_waves_per_eu(5)))
-k_lj_cand<float, 1>(BatchDev bd, int all_images, int variant)
+k_lj_one<float>(BatchDev bd, int all_images, int variant)
 {
-    lj_cand_loop<float, 1>(bd, all_images, variant);
+    lj_one_loop<float>(bd, all_images, variant);
+}
+
+// Bands of several lanes per atom: every count in one launch (a launch per count leaves
+// each nearly empty in a batch: 64 bands 58 -> 73 ms per 32 steps).
+template <typename T>
+__global__ void __launch_bounds__(CFNEB_TILE) __attribute__((amdgpu_waves_per_eu(4)))
+k_lj_lanes(BatchDev bd, int all_images, int variant)
+{
+    ItemLoopRO loop(bd, KIND_LJK, all_images);
+    Item it;
+    while (loop.next(it)) {
+        const BandDev b = band_ro(bd, it.band);
+        const cmem<BandState>* sr = cp(b.st);
+        if (int(band_variant(b) != variant) | int(band_stopped(sr))) continue;  // uniform over the block
+        const int slot = sr->slot[it.image];
+        switch (b.lj_lanes) {  // uniform over the block
+        case 2: lj_item<T, 2>(b, b.st, slot, it.tile); break;
+        case 4: lj_item<T, 4>(b, b.st, slot, it.tile); break;
+        case 8: lj_item<T, 8>(b, b.st, slot, it.tile); break;
+        case 16: lj_item<T, 16>(b, b.st, slot, it.tile); break;
+        default: lj_item<T, 32>(b, b.st, slot, it.tile); break;
+        }
+    }
 }
 
 template <typename T>
 void launch_lj(const Launch& L, int all_images, int variant, hipStream_t s)
 {
-    // one launch per lane count present (each skips the bands of the other counts)
     const unsigned g = L.g_force;
-    if (L.variants & (1u << 8)) k_lj_cand<T, 1><<<g, CFNEB_TILE, 0, s>>>(L.bd, all_images, variant);
-    if (L.variants & (1u << 9)) k_lj_cand<T, 2><<<g, CFNEB_TILE, 0, s>>>(L.bd, all_images, variant);
-    if (L.variants & (1u << 10)) k_lj_cand<T, 4><<<g, CFNEB_TILE, 0, s>>>(L.bd, all_images, variant);
-    if (L.variants & (1u << 11)) k_lj_cand<T, 8><<<g, CFNEB_TILE, 0, s>>>(L.bd, all_images, variant);
+    if (L.variants & (1u << 8)) k_lj_one<T><<<g, CFNEB_TILE, 0, s>>>(L.bd, all_images, variant);
+    if (L.variants & (1u << 9)) k_lj_lanes<T><<<g, CFNEB_TILE, 0, s>>>(L.bd, all_images, variant);
 }
 
 // ------------------------------------------------------------ per-image reduction

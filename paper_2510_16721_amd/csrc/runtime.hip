@@ -24,11 +24,16 @@ constexpr double kEvPerA3InGPa = 160.21766208;
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
-    int N, ld, Mcap, ntA, ntR, ntR4, nbcap, cap, ccap, fp64, tersoff;
+    int N, ld, Mcap, ntA, ntF, ntR, ntR4, nbcap, cap, ccap, fp64, tersoff;
     size_t X, V, R, S, F, FN, binfo, bcount, bstart, bpos, nbr, ncnt, cand, ncand, Rref, skin, dvec, bo, bcid, P, crev, geom,
         scal, dotred, skmax,
         evpart, dotpart, maxpart, refpart, staging, state, table, live, plan, total;
 };
+
+// Fewest atoms of an LJ force item that the workspace has room for (partial sums of each
+// item's waves), by atoms alone: lanes beyond it cover an item in several passes.  Bands
+// too large to want many lanes keep the room of 256-atom items.
+int lj_least_tile(int atoms) { return atoms <= 8192 ? 8 : atoms <= 32768 ? 64 : CFNEB_TILE; }
 
 bool make_layout(const cfneb_params* p, int64_t n_atoms, int max_images, Layout* L)
 {
@@ -39,6 +44,7 @@ bool make_layout(const cfneb_params* p, int64_t n_atoms, int max_images, Layout*
     L->ld = ((L->N + 3 + 63) / 64) * 64;
     L->Mcap = max_images;
     L->ntA = (L->N + CFNEB_TILE - 1) / CFNEB_TILE;
+    L->ntF = p->potential == CFNEB_LJ ? (L->N + lj_least_tile(L->N) - 1) / lj_least_tile(L->N) : L->ntA;
     L->ntR = (L->N + 3 + CFNEB_TILE - 1) / CFNEB_TILE;
     L->ntR4 = (L->N + 3 + CFNEB_TILE4 - 1) / CFNEB_TILE4;
     L->nbcap = L->N + 64;
@@ -84,7 +90,7 @@ bool make_layout(const cfneb_params* p, int64_t n_atoms, int max_images, Layout*
     L->crev = take(L->tersoff ? M * size_t(L->ccap) * N * 4 : 0);
     L->geom = take(M * sizeof(ImageGeom));
     L->scal = take(M * sizeof(ImageScal));
-    L->evpart = take(M * L->ntA * CFNEB_WAVES * 10 * 8);
+    L->evpart = take(M * L->ntF * CFNEB_WAVES * 10 * 8);
     L->dotred = take(M * CFNEB_NDOT * 8);
     L->dotpart = take(M * L->ntR4 * CFNEB_WAVES * CFNEB_NDOT * 8);
     L->maxpart = take(M * L->ntR4 * 3 * 8);
@@ -102,15 +108,15 @@ bool make_layout(const cfneb_params* p, int64_t n_atoms, int max_images, Layout*
 
 // Lanes sharing an atom in the LJ force kernel, a property of the band: from the
 // table that tune_lanes.py measures (fastest lane count of a band stepped alone, by
-// atoms x images), or CFNEB_LJ_LANES.
+// atoms x moving images), or CFNEB_LJ_LANES.
 int lj_lanes_for(long long atoms, int images)
 {
     const char* v = std::getenv("CFNEB_LJ_LANES");
     if (v) {
         const int k = std::atoi(v);
-        if (k == 1 || k == 2 || k == 4 || k == 8) return k;
+        if (k == 1 || k == 2 || k == 4 || k == 8 || k == 16 || k == 32) return k;
     }
-    const long long work = atoms * images;
+    const long long work = atoms * (images - 2);
     for (const auto& e : kLjLanesTable)
         if (work <= e.max_atom_images) return e.lanes;
     return 1;
@@ -118,7 +124,7 @@ int lj_lanes_for(long long atoms, int images)
 
 // Grids of a band table, bounded by the most items its bands can hold.
 void size_grids(Launch& L, long long atom_tiles, long long row_tiles, long long bin_tiles, long long images,
-                int bands, long long atom4_tiles, long long row4_tiles)
+                int bands, long long atom4_tiles, long long row4_tiles, long long force_tiles)
 {
     L.g[KIND_ATOM4] = grid_for(atom4_tiles, CFNEB_GRID_TILES);
     L.g[KIND_ROW4] = grid_for(row4_tiles, CFNEB_GRID_TILES);
@@ -130,7 +136,8 @@ void size_grids(Launch& L, long long atom_tiles, long long row_tiles, long long 
     L.g[KIND_IVAL] = grid_for(row_tiles, CFNEB_GRID_TILES);
     L.g[KIND_SLOTROW] = grid_for(row_tiles, CFNEB_GRID_TILES);
     L.g[KIND_BAND] = grid_for(bands, CFNEB_GRID_BANDS);
-    L.g_force_tile = grid_for(atom_tiles, CFNEB_GRID_FORCE);
+    L.g[KIND_LJ1] = L.g[KIND_LJK] = L.g[KIND_TS] = grid_for(force_tiles, CFNEB_GRID_TILES);
+    L.g_force_tile = grid_for(force_tiles, CFNEB_GRID_FORCE);
     L.g_force = L.g_force_tile;
 }
 
@@ -244,6 +251,8 @@ void fill_dev(cfneb_band* b, void* ws, const double* h0, int relax)
     d.rcl2 = d.rcl * d.rcl;
     d.lj_eps = p->lj_eps;
     d.lj_lanes = lj_lanes_for(L.N, p->n_images);
+    d.lj_tile = std::max(CFNEB_TILE / d.lj_lanes, lj_least_tile(L.N));
+    d.ntF = p->potential == CFNEB_LJ ? (L.N + d.lj_tile - 1) / d.lj_tile : L.ntA;
     d.lj_sig2 = p->lj_sigma * p->lj_sigma;
     if (p->lj_shift) {
         const double q = d.lj_sig2 / (p->lj_rc * p->lj_rc);
@@ -337,7 +346,7 @@ void fill_dev(cfneb_band* b, void* ws, const double* h0, int relax)
     ln.bd.cap = 1;
     const long long M = L.Mcap;
     size_grids(ln, M * L.ntA, M * L.ntR, M * ((L.nbcap + CFNEB_TILE - 1) / CFNEB_TILE), M, 1,
-               M * ((L.N + CFNEB_TILE4 - 1) / CFNEB_TILE4), M * L.ntR4);
+               M * ((L.N + CFNEB_TILE4 - 1) / CFNEB_TILE4), M * L.ntR4, M * d.ntF);
     ln.variants = launch_variants(d);
 }
 
@@ -407,7 +416,7 @@ int launch_step_direct(cfneb_band* b, bool with_refine)
 // per grid, timed with HIP events on the table's stream.
 int tune_force_grid(Launch& L, hipStream_t s)
 {
-    const unsigned cand[2] = {L.g[KIND_ATOM], L.g_force_tile};
+    const unsigned cand[2] = {L.g[KIND_TS], L.g_force_tile};
     // CFNEB_FORCE_GRID=persistent|tile fixes the choice (tests, reproducible timing)
     const char* fixed = std::getenv("CFNEB_FORCE_GRID");
     if (fixed && (std::strcmp(fixed, "persistent") == 0 || std::strcmp(fixed, "tile") == 0)) {
@@ -1264,7 +1273,8 @@ int cfneb_batch_create(int max_bands, void* workspace, size_t workspace_bytes, v
     B->launch.bd.plan = B->plan;
     B->launch.bd.cap = max_bands;
     // any band may join later: size the persistent grids for the whole chip
-    size_grids(B->launch, 1LL << 40, 1LL << 40, 1LL << 40, 1LL << 40, max_bands, 1LL << 40, 1LL << 40);
+    size_grids(B->launch, 1LL << 40, 1LL << 40, 1LL << 40, 1LL << 40, max_bands, 1LL << 40, 1LL << 40,
+               1LL << 40);
     B->launch.variants = 0;
     const char* ng = std::getenv("CFNEB_NO_GRAPH");
     B->use_graph = !(ng && ng[0] == '1');

@@ -507,7 +507,7 @@ __device__ void ts_filter_bonds_loop(const BatchDev& bd, int all_images, int var
 {
     __shared__ vec4_t<T> lbond[TS_LDS_BONDS * CFNEB_TILE];
     __shared__ int lcid[TS_LDS_BONDS * CFNEB_TILE];
-    ItemLoopRO loop(bd, KIND_ATOM, all_images);
+    ItemLoopRO loop(bd, KIND_TS, all_images);
     Item it;
     while (loop.next(it)) {
         const BandDev b = band_ro(bd, it.band);
@@ -550,7 +550,7 @@ __device__ void ts_gather_item(const BandDev& b, BandState* st, int slot, int i)
 template <typename T>
 __global__ void __launch_bounds__(CFNEB_TILE) k_ts_gather(BatchDev bd, int all_images, int variant)
 {
-    ItemLoopRO loop(bd, KIND_ATOM, all_images);
+    ItemLoopRO loop(bd, KIND_TS, all_images);
     Item it;
     while (loop.next(it)) {
         const BandDev b = band_ro(bd, it.band);

@@ -1,7 +1,7 @@
-"""Autotuner of the LJ force kernel's lanes per atom (1, 2, 4 or 8 lanes of a
-wavefront share one atom's candidates).
+"""Autotuner of the LJ force kernel's lanes per atom (1, 2, 4 .. 32 lanes of
+a wavefront share one atom's candidates).
 
-For LJ FCC vacancy-hop bands over a range of sizes (atoms x images), each lane
+For LJ FCC vacancy-hop bands over a range of sizes (atoms x moving images), each lane
 count is timed on the band stepped alone (HIP-event phase timing of the force
 stage, cfneb_step_profiled); the fastest count per size becomes a row of
 csrc/lj_lanes_table.h, which the library compiles in and looks up at band
@@ -19,9 +19,13 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "csrc", "lj_lanes_table.h")
-LANES = (1, 2, 4, 8)
-# (FCC cells per edge, images): 31 .. 97,555 atoms, 217 .. 2.3M atom-images
-CASES = [(2, 7), (3, 7), (4, 7), (6, 7), (8, 7), (11, 7), (16, 7), (22, 7), (29, 7), (29, 24)]
+LANES = (1, 2, 4, 8, 16, 32)
+# More lanes cost throughput where a batch fills the chip anyway (per atom 9 % for 2 lanes,
+# 20 % for 4, 65 % for 16), so a count has to gain more than this on the band alone.
+MARGIN = 0.16
+# (FCC cells per edge, images): 31 .. 97,555 atoms, 155 .. 2.1M atoms x moving images
+CASES = [(2, 7), (4, 3), (4, 7), (5, 7), (6, 7), (10, 3), (8, 7), (8, 11), (11, 7), (14, 7), (16, 7), (16, 11),
+         (22, 7), (29, 7), (29, 24)]
 
 
 def _band(n, images):
@@ -59,7 +63,7 @@ def pick(t, margin=0.03):
 def table_rows(results):
     """results: [(atom_images, {lanes: ms})] -> [(max_atom_images, lanes)], thresholds at
     the geometric mean of neighbouring sizes whose picked counts differ."""
-    pts = sorted((w, pick(t)) for w, t in results)
+    pts = sorted((w, pick(t, MARGIN)) for w, t in results)
     rows = []
     for i, (w, k) in enumerate(pts):
         if i + 1 < len(pts) and pts[i + 1][1] == k:
@@ -72,12 +76,13 @@ def table_rows(results):
 
 
 def write_table(rows, results, path=TABLE):
-    lines = ["// LJ lanes per atom by band size (atoms x images at creation): the fastest lane",
+    lines = ["// LJ lanes per atom by band size (atoms x moving images at creation): the fastest lane",
              "// count of an FP32 LJ band stepped alone.  Written by tune_lanes.py from",
-             "// force-stage times (us per step) of LJ FCC vacancy-hop bands:"]
+             "// force-stage times (us per step) of LJ FCC vacancy-hop bands (the fewest lanes",
+             f"// within {100 * MARGIN:.0f} % of the fastest):"]
     for w, t in sorted(results):
         lines.append("//   " + f"{w:>9d} atom-images: " +
-                     "  ".join(f"{k}: {1000 * t[k]:8.1f}" for k in LANES))
+                     "  ".join(f"{k}: {1000 * t[k]:8.1f}" for k in LANES if k in t))
     lines += ["#ifndef CFNEB_LJ_LANES_TABLE_H", "#define CFNEB_LJ_LANES_TABLE_H", "",
               "struct LjLanesEntry {", "    long long max_atom_images;", "    int lanes;", "};",
               "static const LjLanesEntry kLjLanesTable[] = {"]
@@ -99,8 +104,8 @@ def main(argv=None):
     results = []
     for n, images in CASES:
         atoms, t = time_case(n, images)
-        results.append((atoms * images, t))
-        print(f"tune_lanes: {atoms} atoms x {images} images: " +
+        results.append((atoms * (images - 2), t))
+        print(f"tune_lanes: {atoms} atoms x {images - 2} moving images: " +
               "  ".join(f"K={k} {1000 * t[k]:.1f} us" for k in LANES), flush=True)
     rows = table_rows(results)
     print("tune_lanes: table", rows, flush=True)
