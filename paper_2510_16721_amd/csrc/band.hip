@@ -245,6 +245,7 @@ __device__ void scalars_item(const BandDev& b, BandState* st)
         }
         ci_s = ci;
         st->ci = ci;
+        st->move = 0;  // the geometry and skin passes have applied the pending move
     }
     __syncthreads();
     // one thread per moving image: tangent, projection coefficients, FIRE terms

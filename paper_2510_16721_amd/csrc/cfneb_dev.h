@@ -42,6 +42,11 @@
 // atoms; 22 images of 97,555: 821 us with 192 atoms, 923 us with 96).
 #define CFNEB_TILE_CAND 128
 #define CFNEB_TILE4 1024         // rows (atoms) of a streaming item with 4 per thread
+// Bands of up to this many atoms have their positions, skin test and bins done by one
+// block per image (k_skin_image) instead of six launches (4,608 atoms: 15 against 24 us a
+// step; a block needs 4 us per further 4,096 atoms, the launches' fixed part is 20 us).
+// Above, the bins would not fit in LDS.
+#define CFNEB_SKIN_IMAGE 8192
 #define CFNEB_WAVES 4            // waves per block of CFNEB_TILE threads
 #define CFNEB_NDOT 22            // band-dot partial sums per moving image and row tile
 #define CFNEB_NPROF 14           // energy-profile partial sums per image and row tile
@@ -362,12 +367,15 @@ __device__ inline bool band_stopped(const cmem<BandState>* st) { return (st->don
 enum ItemKind {
     KIND_ATOM = 0,  // 256-atom tiles x images
     KIND_ROW,       // 256-row tiles (N + 3 rows) x images
-    KIND_BIN,       // 256-bin tiles x images
+    KIND_BIN,       // 256-bin tiles x images, large bands
     KIND_IMAGE,     // one item per image
     KIND_IVAL,      // 256-row tiles x intervals between consecutive images
     KIND_SLOTROW,   // 256-row tiles x every image slot of the capacity
     KIND_BAND,      // one item per band
-    KIND_ATOM4,     // 1024-atom tiles x images (4 atoms per thread)
+    KIND_ATOM4,     // 1024-atom tiles x images (4 atoms per thread), large bands
+    KIND_LATOM,     // 256-atom tiles x images, large bands (more than CFNEB_SKIN_IMAGE atoms)
+    KIND_LIMAGE,    // one item per image, large bands
+    KIND_SIMAGE,    // one item per image, the other bands
     KIND_ROW4,      // 1024-row tiles x images (4 rows per thread)
     // items of the energy-forming force kernels (ntF) x images, each kind holding only
     // the bands that its kernel serves (a kernel that walks the items of other bands to
@@ -401,17 +409,22 @@ struct Item {
     int band, tile, image;
 };
 
+__host__ __device__ inline bool skin_by_image(const BandDev& b) { return b.N <= CFNEB_SKIN_IMAGE; }
+
 __device__ inline int kind_tiles(const BandDev& b, int kind)
 {
     switch (kind) {
     case KIND_ATOM: return b.ntA;
-    case KIND_ATOM4: return (b.N + CFNEB_TILE4 - 1) / CFNEB_TILE4;
+    case KIND_ATOM4: return skin_by_image(b) ? 0 : (b.N + CFNEB_TILE4 - 1) / CFNEB_TILE4;
+    case KIND_LATOM: return skin_by_image(b) ? 0 : b.ntA;
+    case KIND_LIMAGE: return skin_by_image(b) ? 0 : 1;
+    case KIND_SIMAGE: return skin_by_image(b) ? 1 : 0;
     case KIND_ROW4: return b.ntR4;
     case KIND_LJ1: return b.potential == CFNEB_LJ && b.lj_lanes == 1 ? b.ntF : 0;
     case KIND_LJK: return b.potential == CFNEB_LJ && b.lj_lanes > 1 ? b.ntF : 0;
     case KIND_TS: return b.potential == CFNEB_TERSOFF_C ? b.ntF : 0;
     case KIND_CAND: return (b.N + CFNEB_TILE_CAND - 1) / CFNEB_TILE_CAND;
-    case KIND_BIN: return (b.nbcap + CFNEB_TILE - 1) / CFNEB_TILE;
+    case KIND_BIN: return skin_by_image(b) ? 0 : (b.nbcap + CFNEB_TILE - 1) / CFNEB_TILE;
     case KIND_ROW:
     case KIND_IVAL:
     case KIND_SLOTROW: return b.ntR;
@@ -571,7 +584,12 @@ __host__ __device__ inline unsigned lanes_bit(const BandDev& b)
     if (b.potential != CFNEB_LJ) return 0u;
     return b.lj_lanes == 1 ? 1u << 8 : 1u << 9;
 }
-__host__ __device__ inline unsigned launch_variants(const BandDev& b) { return (1u << band_variant(b)) | lanes_bit(b); }
+// Bits 10 and 11: bands whose skin test takes one block per image, and larger ones.
+enum { VARIANT_SKIN_IMAGE = 10, VARIANT_SKIN_LARGE };
+__host__ __device__ inline unsigned launch_variants(const BandDev& b)
+{
+    return (1u << band_variant(b)) | lanes_bit(b) | (1u << (skin_by_image(b) ? VARIANT_SKIN_IMAGE : VARIANT_SKIN_LARGE));
+}
 
 // Launch geometry of one batch: the grid of each kind, bounded by the most items
 // the table can ever hold, and the variants present.

@@ -14,7 +14,8 @@
 // R_ref is kept in FP32: each component within 2^-24 of its magnitude, so d_i measured
 // against it is within 2^-24 |R_ref,i| (1 + |E|) of the true one, added to the bound.
 //
-// Kernels, in order (each a persistent walk over the items of every live band):
+// Kernels, in order (each a persistent walk over the items of every live band); bands of
+// up to CFNEB_SKIN_IMAGE atoms take k_skin_image instead of all before k_cand:
 //   k_skin_check   (steps) the previous step's move of the atom rows; R = R~ D (and
 //                  its fixed-point fractional coordinates); max_i d_i^2 per 1024-atom tile
 //   k_skin_decide  max over an image's tiles, rebuild flag per image; a rebuild takes
@@ -69,16 +70,106 @@ __device__ inline uint4 fixed_fraction(const double* r, const double* hi)
     return make_uint4(u[0], u[1], u[2], 0u);
 }
 
-// 1024 atoms per item, four per thread: all loads of the four atoms are issued before
-// any position is stored.  In a step, first the previous step's pending move of these
-// atom rows (X += scale dt v', written back); R = R~ D (and its fixed-point fractional
-// coordinates for FP32 LJ bands); d_i^2 against the strained reference when a list
-// exists; the tile's maximum goes to its own slot (no atomics: many tiles per image
-// would contend on one address).
+// Four atoms i0, i0 + stride, ..: all loads are issued before any position is stored.  In
+// a step, first the previous step's pending move of these atom rows (X += scale dt v',
+// written back); R = R~ D (and its fixed-point fractional coordinates for FP32 LJ bands);
+// m[0], m[1]: maximum of d_i^2 against the strained FP32 reference when a list exists
+// (valid), and of |R_ref,i|^2 for its rounding.
+struct SkinFrame {
+    double D[9], E[9], hi[9];
+    bool valid;
+};
+__device__ inline void skin_atoms(const BandDev& b, const cmem<BandState>* st, int slot, const SkinFrame& f, int i0,
+                                  int stride, int all_images, double (&m)[2])
+{
+    constexpr int Q = CFNEB_TILE4 / CFNEB_TILE;
+    gmem<uint32_t>* __restrict__ S = b.S ? gp(Ss(b, slot)) : nullptr;
+    gmem<double>* __restrict__ X = gp(Xs(b, slot));
+    const gmem<const float>* __restrict__ Rr = gp<const float>(b.Rref + size_t(slot) * slot_rows(b));
+    double x[Q][3], a[Q][3];
+    if (move_pending(st, all_images)) {  // uniform over the block
+        // the previous step's move of these rows: X += scale (dt v')
+        const gmem<const double>* __restrict__ V = gp<const double>(Vs(b, st->vcur, slot));
+        const double sc = st->scale, dt = st->dt;
+        double v[Q][3];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = i0 + q * stride;
+            const bool in = i < b.N;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x[q][c] = in ? X[size_t(c) * b.ld + i] : 0.0;
+                v[q][c] = in ? V[size_t(c) * b.ld + i] : 0.0;
+                a[q][c] = (in && f.valid) ? double(Rr[size_t(c) * b.ld + i]) : 0.0;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = i0 + q * stride;
+            if (i >= b.N) continue;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x[q][c] += sc * (dt * v[q][c]);
+                X[size_t(c) * b.ld + i] = x[q][c];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = i0 + q * stride;
+            const bool in = i < b.N;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x[q][c] = in ? X[size_t(c) * b.ld + i] : 0.0;
+                a[q][c] = (in && f.valid) ? double(Rr[size_t(c) * b.ld + i]) : 0.0;
+            }
+        }
+    }
+    gmem<R3>* __restrict__ R = gp(Rs(b, slot));
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int i = i0 + q * stride;
+        if (i >= b.N) continue;
+        double r[3];
+        for (int c = 0; c < 3; ++c) r[c] = (x[q][0] * f.D[c] + x[q][1] * f.D[3 + c]) + x[q][2] * f.D[6 + c];
+        store3(R, i, r[0], r[1], r[2]);
+        if (S) {
+            const uint4 w = fixed_fraction(r, f.hi);
+            S[3 * size_t(i)] = w.x;
+            S[3 * size_t(i) + 1] = w.y;
+            S[3 * size_t(i) + 2] = w.z;
+        }
+        if (f.valid) {
+            double d2 = 0.0;
+            for (int c = 0; c < 3; ++c) {
+                const double ref = a[q][c] + ((a[q][0] * f.E[c] + a[q][1] * f.E[3 + c]) + a[q][2] * f.E[6 + c]);
+                const double d = r[c] - ref;
+                d2 += d * d;
+            }
+            m[0] = fmax(m[0], d2);
+            m[1] = fmax(m[1], (a[q][0] * a[q][0] + a[q][1] * a[q][1]) + a[q][2] * a[q][2]);
+        }
+    }
+}
+__device__ inline SkinFrame skin_frame(const BandDev& b, int slot)
+{
+    const cmem<ImageGeom>* g = cp(b.geom + slot);
+    SkinFrame f;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        f.D[q] = g->D[q];
+        f.E[q] = g->E[q];
+        f.hi[q] = g->hinv[q];
+    }
+    f.valid = cp(b.skst + slot)->valid != 0;
+    return f;
+}
+
+// Large bands: 1024 atoms per item, four per thread; the tile's maxima go to its own slot
+// (no atomics: many tiles per image would contend on one address).
 __global__ void __launch_bounds__(CFNEB_TILE) k_skin_check(BatchDev bd, int all_images)
 {
     __shared__ double lds[(CFNEB_TILE / 64) * 2];
-    constexpr int Q = CFNEB_TILE4 / CFNEB_TILE;
     ItemLoopRO loop(bd, KIND_ATOM4, all_images);
     Item it;
     while (loop.next(it)) {
@@ -86,84 +177,9 @@ __global__ void __launch_bounds__(CFNEB_TILE) k_skin_check(BatchDev bd, int all_
         const cmem<BandState>* st = cp(b.st);
         if (band_stopped(st)) continue;  // uniform over the block
         const int slot = st->slot[it.image];
-        const cmem<ImageGeom>* g = cp(b.geom + slot);
-        double D[9], E[9], hi[9];
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            D[q] = g->D[q];
-            E[q] = g->E[q];
-            hi[q] = g->hinv[q];
-        }
-        const bool valid = cp(b.skst + slot)->valid != 0;
-        gmem<uint32_t>* __restrict__ S = b.S ? gp(Ss(b, slot)) : nullptr;
-        gmem<double>* __restrict__ X = gp(Xs(b, slot));
-        const gmem<const float>* __restrict__ Rr = gp<const float>(b.Rref + size_t(slot) * slot_rows(b));
-        double x[Q][3], a[Q][3];
-        if (move_pending(st, all_images)) {  // uniform over the block
-            // the previous step's move of these rows: X += scale (dt v')
-            const gmem<const double>* __restrict__ V = gp<const double>(Vs(b, st->vcur, slot));
-            const double sc = st->scale, dt = st->dt;
-            double v[Q][3];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int i = it.tile * CFNEB_TILE4 + q * CFNEB_TILE + threadIdx.x;
-                const bool in = i < b.N;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    x[q][c] = in ? X[size_t(c) * b.ld + i] : 0.0;
-                    v[q][c] = in ? V[size_t(c) * b.ld + i] : 0.0;
-                    a[q][c] = (in && valid) ? double(Rr[size_t(c) * b.ld + i]) : 0.0;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int i = it.tile * CFNEB_TILE4 + q * CFNEB_TILE + threadIdx.x;
-                if (i >= b.N) continue;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    x[q][c] += sc * (dt * v[q][c]);
-                    X[size_t(c) * b.ld + i] = x[q][c];
-                }
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int i = it.tile * CFNEB_TILE4 + q * CFNEB_TILE + threadIdx.x;
-                const bool in = i < b.N;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    x[q][c] = in ? X[size_t(c) * b.ld + i] : 0.0;
-                    a[q][c] = (in && valid) ? double(Rr[size_t(c) * b.ld + i]) : 0.0;
-                }
-            }
-        }
-        // max d_i^2 against the FP32 reference, and max |R_ref,i|^2 for its rounding
+        const SkinFrame f = skin_frame(b, slot);
         double m[2] = {0.0, 0.0};
-        gmem<R3>* __restrict__ R = gp(Rs(b, slot));
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int i = it.tile * CFNEB_TILE4 + q * CFNEB_TILE + threadIdx.x;
-            if (i >= b.N) continue;
-            double r[3];
-            for (int c = 0; c < 3; ++c) r[c] = (x[q][0] * D[c] + x[q][1] * D[3 + c]) + x[q][2] * D[6 + c];
-            store3(R, i, r[0], r[1], r[2]);
-            if (S) {
-                const uint4 f = fixed_fraction(r, hi);
-                S[3 * size_t(i)] = f.x;
-                S[3 * size_t(i) + 1] = f.y;
-                S[3 * size_t(i) + 2] = f.z;
-            }
-            if (valid) {
-                double d2 = 0.0;
-                for (int c = 0; c < 3; ++c) {
-                    const double ref = a[q][c] + ((a[q][0] * E[c] + a[q][1] * E[3 + c]) + a[q][2] * E[6 + c]);
-                    const double d = r[c] - ref;
-                    d2 += d * d;
-                }
-                m[0] = fmax(m[0], d2);
-                m[1] = fmax(m[1], (a[q][0] * a[q][0] + a[q][1] * a[q][1]) + a[q][2] * a[q][2]);
-            }
-        }
+        skin_atoms(b, st, slot, f, it.tile * CFNEB_TILE4 + int(threadIdx.x), CFNEB_TILE, all_images, m);
         block_max<2>(m, lds);
         if (threadIdx.x == 0) {
             double* out = b.skmax + (size_t(slot) * kind_tiles(b, KIND_ATOM4) + it.tile) * 2;
@@ -171,6 +187,30 @@ __global__ void __launch_bounds__(CFNEB_TILE) k_skin_check(BatchDev bd, int all_
             out[1] = m[1];
         }
     }
+}
+
+// The decision for one image from its maxima; a rebuild takes the current cell as
+// reference.  Returns whether the image rebuilds its candidates.
+__device__ inline bool skin_decision(const BatchDev& bd, const BandDev& b, int slot, const double (&m)[2])
+{
+    SkinState& sk = b.skst[slot];
+    const ImageGeom& g = b.geom[slot];
+    bool rebuild = true;
+    // the FP32 reference is within 2^-24 |R_ref,i| of the build positions, so every
+    // displacement is within that times (1 + |E|) of the one measured against it
+    const double dmax = sqrt(m[0]) + 0x1p-24 * (1.0 + 1e-6) * sqrt(m[1]) * (1.0 + g.enorm);
+    if (b.skin > 0.0 && sk.valid) rebuild = !(2.0 * dmax + b.rcl * g.enorm < b.skin * (1.0 - 1e-6));
+    sk.rebuild = rebuild ? 1 : 0;
+    if (rebuild) {
+        for (int q = 0; q < 9; ++q) {
+            sk.href[q] = g.h[q];
+            sk.hrefinv[q] = g.hinv[q];
+        }
+        sk.far = 0;
+        sk.valid = 1;
+        *rebuild_flag(bd) = 1;
+    }
+    return rebuild;
 }
 
 // One block per band, sixteen threads per image: the maximum over the image's tile
@@ -181,53 +221,34 @@ __global__ void __launch_bounds__(16 * CFNEB_MAX_IMAGES) k_skin_decide(BatchDev 
     Item it;
     while (loop.next(it)) {
         const BandDev& b = bd.bands[it.band];
-        BandState* st = b.st;
+        if (skin_by_image(b)) continue;
+        const BandState* st = b.st;
         const int k = threadIdx.x >> 4, lane = threadIdx.x & 15;
-        // the geometry and skin passes have applied the pending move
-        if (threadIdx.x == 0 && all_images == 0) st->move = 0;
         const bool act = !band_stopped(st) && k < b.Mcap && image_active(st, k, all_images);
         const int slot = act ? st->slot[k] : 0;
         const int nt = kind_tiles(b, KIND_ATOM4);
-        double m = 0.0, ma = 0.0;
+        double m[2] = {0.0, 0.0};
         if (act) {
             const gmem<const double>* mx = gp<const double>(b.skmax + size_t(slot) * nt * 2);
 #pragma unroll 4
             for (int t = lane; t < nt; t += 16) {
-                m = fmax(m, mx[2 * t]);
-                ma = fmax(ma, mx[2 * t + 1]);
+                m[0] = fmax(m[0], mx[2 * t]);
+                m[1] = fmax(m[1], mx[2 * t + 1]);
             }
         }
         for (int off = 8; off > 0; off >>= 1) {
-            m = fmax(m, __shfl_xor(m, off, 16));
-            ma = fmax(ma, __shfl_xor(ma, off, 16));
+            m[0] = fmax(m[0], __shfl_xor(m[0], off, 16));
+            m[1] = fmax(m[1], __shfl_xor(m[1], off, 16));
         }
-        if (!act || lane != 0) continue;
-        SkinState& sk = b.skst[slot];
-        const ImageGeom& g = b.geom[slot];
-        bool rebuild = true;
-        // the FP32 reference is within 2^-24 |R_ref,i| of the build positions, so every
-        // displacement is within that times (1 + |E|) of the one measured against it
-        const double dmax = sqrt(m) + 0x1p-24 * (1.0 + 1e-6) * sqrt(ma) * (1.0 + g.enorm);
-        if (b.skin > 0.0 && sk.valid) rebuild = !(2.0 * dmax + b.rcl * g.enorm < b.skin * (1.0 - 1e-6));
-        sk.rebuild = rebuild ? 1 : 0;
-        if (rebuild) {
-            for (int q = 0; q < 9; ++q) {
-                sk.href[q] = g.h[q];
-                sk.hrefinv[q] = g.hinv[q];
-            }
-            sk.far = 0;
-            sk.valid = 1;
-            *rebuild_flag(bd) = 1;
-        }
+        if (act && lane == 0) skin_decision(bd, b, slot, m);
     }
 }
 
-__device__ void bin_assign_item(const BandDev& b, int slot, int i)
+// Bin of an atom and the lattice image it lies in, from its position.
+__device__ inline int bin_of(const ImageGeom& g, const double4& ri, int (&img)[3])
 {
-    const ImageGeom& g = b.geom[slot];
-    const double4 ri = load4(gp<const R3>(Rs(b, slot)), i);
     const double r[3] = {ri.x, ri.y, ri.z};
-    int bi[3], img[3];
+    int bi[3];
     for (int q = 0; q < 3; ++q) {
         const double s = (r[0] * g.hinv[q] + r[1] * g.hinv[3 + q]) + r[2] * g.hinv[6 + q];
         double fl = floor(s);
@@ -238,20 +259,128 @@ __device__ void bin_assign_item(const BandDev& b, int slot, int i)
         bq = bq < 0 ? 0 : (bq >= g.nb[q] ? g.nb[q] - 1 : bq);
         bi[q] = bq;
     }
-    const int bin = (bi[0] * g.nb[1] + bi[1]) * g.nb[2] + bi[2];
+    return (bi[0] * g.nb[1] + bi[1]) * g.nb[2] + bi[2];
+}
+__device__ inline int pack_binfo_image(const int (&img)[3])
+{
+    return (img[0] + 512) | ((img[1] + 512) << 10) | ((img[2] + 512) << 20);
+}
+__device__ inline bool image_is_far(const int (&img)[3])
+{
+    return abs(img[0]) > 3 || abs(img[1]) > 3 || abs(img[2]) > 3;
+}
+// Atom i's record in bin order.
+__device__ inline BinAtom bin_record(const ImageGeom& g, const double4& ri, int i, int im)
+{
+    const double n0 = img_n(im, 0), n1 = img_n(im, 1), n2 = img_n(im, 2);
+    BinAtom a;
+    a.x = float(ri.x - (n0 * g.h[0] + n1 * g.h[3] + n2 * g.h[6]));
+    a.y = float(ri.y - (n0 * g.h[1] + n1 * g.h[4] + n2 * g.h[7]));
+    a.z = float(ri.z - (n0 * g.h[2] + n1 * g.h[5] + n2 * g.h[8]));
+    a.code = uint32_t(i) | pack_images(-img_n(im, 0), -img_n(im, 1), -img_n(im, 2));
+    return a;
+}
+
+// Bands of up to CFNEB_SKIN_IMAGE atoms: one block per image takes the positions, the skin
+// test, the decision and, on a rebuild, the bins in bin order, sorted by id: counts, starts
+// and the atoms of each bin are in LDS, so the phases that are launches of their own for
+// large bands (four of them idle on most steps) are block barriers here.  Latency-bound.
+// Skin test and idle bin launches per step: 4,608 carbon atoms x 22 images 24 -> 15 us,
+// 255 LJ atoms x 5 images 15 -> 7 us.
+__global__ void __launch_bounds__(1024) k_skin_image(BatchDev bd, int all_images)
+{
+    __shared__ double lds[16 * 2];
+    __shared__ int start[CFNEB_SKIN_IMAGE + 64 + 1];
+    __shared__ unsigned short ids[CFNEB_SKIN_IMAGE];
+    __shared__ int wsum[16];
+    __shared__ int rebuild;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    ItemLoopRO loop(bd, KIND_SIMAGE, all_images);
+    Item it;
+    while (loop.next(it)) {
+        const BandDev b = band_ro(bd, it.band);
+        const cmem<BandState>* st = cp(b.st);
+        if (band_stopped(st)) continue;  // uniform over the block
+        const int slot = st->slot[it.image], N = b.N;
+        double m[2] = {0.0, 0.0};
+        {
+            const SkinFrame f = skin_frame(b, slot);
+            for (int i0 = t; i0 - t < N; i0 += 4096) skin_atoms(b, st, slot, f, i0, 1024, all_images, m);
+        }
+        block_max<2>(m, lds);
+        if (t == 0) rebuild = skin_decision(bd, b, slot, m) ? 1 : 0;
+        __syncthreads();
+        if (!rebuild) continue;  // uniform (the next write of the flag is behind barriers)
+        const ImageGeom& g = b.geom[slot];
+        const int nbins = g.nbins;
+        for (int q = t; q <= nbins; q += 1024) start[q] = 0;
+        __syncthreads();
+        int* info = b.binfo + size_t(slot) * 3 * N;
+        const gmem<const R3>* R = gp<const R3>(Rs(b, slot));
+        for (int i = t; i < N; i += 1024) {
+            int img[3];
+            const int bin = bin_of(g, load4(R, i), img);
+            info[i] = bin;
+            info[N + i] = atomicAdd(&start[bin], 1);
+            info[2 * N + i] = pack_binfo_image(img);
+            if (image_is_far(img)) b.skst[slot].far = 1;
+        }
+        __syncthreads();
+        // exclusive scan of the counts, a run of bins per thread
+        const int per = (nbins + 1023) >> 10, q0 = min(t * per, nbins), q1 = min(q0 + per, nbins);
+        int sum = 0;
+        for (int q = q0; q < q1; ++q) sum += start[q];
+        int incl = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += y;
+        }
+        if (lane == 63) wsum[wid] = incl;
+        __syncthreads();
+        int run = incl - sum;
+        for (int w = 0; w < wid; ++w) run += wsum[w];
+        int* gstart = b.bstart + bin_base(b, slot);
+        for (int q = q0; q < q1; ++q) {
+            const int c = start[q];
+            start[q] = run;
+            gstart[q] = run;
+            run += c;
+        }
+        if (t == 0) {
+            start[nbins] = N;
+            gstart[nbins] = N;
+        }
+        __syncthreads();
+        for (int i = t; i < N; i += 1024) ids[start[info[i]] + info[N + i]] = (unsigned short)i;
+        __syncthreads();
+        // an atom's place in its bin is the number of smaller ids there
+        BinAtom* out = b.bpos + size_t(slot) * N;
+        for (int i = t; i < N; i += 1024) {
+            const int bin = info[i];
+            int pos = start[bin];
+            for (int q = start[bin]; q < start[bin + 1]; ++q) pos += int(ids[q]) < i ? 1 : 0;
+            out[pos] = bin_record(g, load4(R, i), i, info[2 * N + i]);
+        }
+        __syncthreads();
+    }
+}
+
+__device__ void bin_assign_item(const BandDev& b, int slot, int i)
+{
+    int img[3];
+    const int bin = bin_of(b.geom[slot], load4(gp<const R3>(Rs(b, slot)), i), img);
     const int rank = atomicAdd(&b.bcount[bin_base(b, slot) + bin], 1);
-    const int packed = (img[0] + 512) | ((img[1] + 512) << 10) | ((img[2] + 512) << 20);
-    int* bi_out = b.binfo + size_t(slot) * 3 * b.N + i;
-    bi_out[0] = bin;
-    bi_out[b.N] = rank;
-    bi_out[2 * size_t(b.N)] = packed;
-    if (abs(img[0]) > 3 || abs(img[1]) > 3 || abs(img[2]) > 3) b.skst[slot].far = 1;
+    int* info = b.binfo + size_t(slot) * 3 * b.N + i;
+    info[0] = bin;
+    info[b.N] = rank;
+    info[2 * size_t(b.N)] = pack_binfo_image(img);
+    if (image_is_far(img)) b.skst[slot].far = 1;
 }
 
 __global__ void __launch_bounds__(CFNEB_TILE) k_bin_assign(BatchDev bd, int all_images)
 {
     if (*rebuild_flag(bd) == 0) return;  // no image rebuilds this step
-    ItemLoop loop(bd, KIND_ATOM, all_images);
+    ItemLoop loop(bd, KIND_LATOM, all_images);
     Item it;
     while (loop.next(it)) {
         const BandDev& b = bd.bands[it.band];
@@ -312,7 +441,7 @@ __device__ void bin_scan_item(const BandDev& b, int slot)
 __global__ void __launch_bounds__(1024) k_bin_scan(BatchDev bd, int all_images)
 {
     if (*rebuild_flag(bd) == 0) return;  // no image rebuilds this step
-    ItemLoop loop(bd, KIND_IMAGE, all_images);
+    ItemLoop loop(bd, KIND_LIMAGE, all_images);
     Item it;
     while (loop.next(it)) {
         const BandDev& b = bd.bands[it.band];
@@ -326,7 +455,7 @@ __global__ void __launch_bounds__(1024) k_bin_scan(BatchDev bd, int all_images)
 __global__ void __launch_bounds__(CFNEB_TILE) k_bin_scatter(BatchDev bd, int all_images)
 {
     if (*rebuild_flag(bd) == 0) return;  // no image rebuilds this step
-    ItemLoop loop(bd, KIND_ATOM, all_images);
+    ItemLoop loop(bd, KIND_LATOM, all_images);
     Item it;
     while (loop.next(it)) {
         const BandDev& b = bd.bands[it.band];
@@ -338,15 +467,7 @@ __global__ void __launch_bounds__(CFNEB_TILE) k_bin_scatter(BatchDev bd, int all
         const int pos = b.bstart[bin_base(b, slot) + binfo_of(b, slot, 0)[i]] + binfo_of(b, slot, 1)[i];
         const int im = binfo_of(b, slot, 2)[i];
         if (pos < 0 || pos >= b.N) continue;
-        const double4 ri = load4(gp<const R3>(Rs(b, slot)), i);
-        const double n0 = img_n(im, 0), n1 = img_n(im, 1), n2 = img_n(im, 2);
-        const double* h = b.geom[slot].h;
-        BinAtom a;
-        a.x = float(ri.x - (n0 * h[0] + n1 * h[3] + n2 * h[6]));
-        a.y = float(ri.y - (n0 * h[1] + n1 * h[4] + n2 * h[7]));
-        a.z = float(ri.z - (n0 * h[2] + n1 * h[5] + n2 * h[8]));
-        a.code = uint32_t(i) | pack_images(-img_n(im, 0), -img_n(im, 1), -img_n(im, 2));
-        b.bpos[size_t(slot) * b.N + pos] = a;
+        b.bpos[size_t(slot) * b.N + pos] = bin_record(b.geom[slot], load4(gp<const R3>(Rs(b, slot)), i), i, im);
     }
 }
 
@@ -813,15 +934,18 @@ void launch_skin_hold(const Launch& L, int hold, hipStream_t s)
 
 void launch_skin(const Launch& L, int all_images, hipStream_t s)
 {
+    if (L.variants & (1u << VARIANT_SKIN_IMAGE)) k_skin_image<<<L.g[KIND_SIMAGE], 1024, 0, s>>>(L.bd, all_images);
+    if (!(L.variants & (1u << VARIANT_SKIN_LARGE))) return;
     k_skin_check<<<L.g[KIND_ATOM4], CFNEB_TILE, 0, s>>>(L.bd, all_images);
     k_skin_decide<<<L.g[KIND_BAND], 16 * CFNEB_MAX_IMAGES, 0, s>>>(L.bd, all_images);
 }
 
 void launch_bins(const Launch& L, int all_images, hipStream_t s)
 {
-    k_bin_assign<<<L.g[KIND_ATOM], CFNEB_TILE, 0, s>>>(L.bd, all_images);
-    k_bin_scan<<<L.g[KIND_IMAGE], 1024, 0, s>>>(L.bd, all_images);
-    k_bin_scatter<<<L.g[KIND_ATOM], CFNEB_TILE, 0, s>>>(L.bd, all_images);
+    if (!(L.variants & (1u << VARIANT_SKIN_LARGE))) return;
+    k_bin_assign<<<L.g[KIND_LATOM], CFNEB_TILE, 0, s>>>(L.bd, all_images);
+    k_bin_scan<<<L.g[KIND_LIMAGE], 1024, 0, s>>>(L.bd, all_images);
+    k_bin_scatter<<<L.g[KIND_LATOM], CFNEB_TILE, 0, s>>>(L.bd, all_images);
     k_bin_sort<<<L.g[KIND_BIN], CFNEB_TILE, 0, s>>>(L.bd, all_images);
 }
 
