@@ -946,13 +946,17 @@ __device__ inline void tersoff_gather(const BandDev& b, int slot, int i0, int st
 // Energy and virial partials of one item of the force kernel: each wave stores its own ten sums
 // (transposed wave reduction, no block barrier).  Every wave of the tile stores, so
 // no partial of an earlier evaluation survives.
+// ADD: onto the wave's stored sums.
+template <bool ADD = false>
 __device__ inline void store_ev_partials(const BandDev& b, int slot, int tile, const double (&v)[10])
 {
     const double s = wave_sum_t<10>(v);
     constexpr int LOGP = wave_sum_logp<10>();
     const int lane = int(threadIdx.x) & 63, idx = lane >> (6 - LOGP);
-    if ((lane & ((64 >> LOGP) - 1)) == 0 && idx < 10)
-        b.evpart[((size_t(slot) * b.ntF + tile) * CFNEB_WAVES + (int(threadIdx.x) >> 6)) * 10 + idx] = s;
+    if ((lane & ((64 >> LOGP) - 1)) == 0 && idx < 10) {
+        double* p = b.evpart + ((size_t(slot) * b.ntF + tile) * CFNEB_WAVES + (int(threadIdx.x) >> 6)) * 10 + idx;
+        *p = ADD ? *p + s : s;
+    }
 }
 
 // ---------------------------------------------------------------- launchers

@@ -177,6 +177,9 @@ struct TersoffT {
     }
 };
 
+// Bonds held in LDS per thread, for atoms with at most this many (carbon: 3 or 4).
+#define TS_LDS_BONDS 4
+
 template <typename T>
 using vec4_t = typename std::conditional<sizeof(T) == 4, float4, double4>::type;
 template <typename T>
@@ -313,8 +316,97 @@ __device__ void ts_atom_regs(const TersoffT<T>& P, const vec4_t<T> (&bond)[MAXB]
     }
 }
 
-// Any number of bonds: bond orders go through the per-bond scratch array; bcid holds
-// each bond's candidate slot.
+// Atoms with more bonds than the registers take: G lanes to an atom (64 / G atoms at once),
+// lane e of the group has bond e (d, cid) and sees the others in increasing order.  One
+// lane walking them through memory held its whole wave, and in a small band the launch: a
+// chain of cnt^2 loads (a 511-atom vacancy hop, whose hopping atom has such a shell:
+// 36 us a launch, 14 us this way; 98,304 atoms,
+// 22 images on their way to diamond: a step 505 -> 406 us).  i, cnt: the group's atom and its bonds (0: idle group);
+// most: the largest cnt of the wave.
+template <typename T, int G>
+__device__ void ts_atom_group(const TersoffT<T>& P, const vec4_t<T>& de, int cid, gmem<P3<T>>* Pout, size_t N, int i,
+                              int cnt, int most, double* acc)
+{
+    const int lane = int(threadIdx.x) & 63, e = lane & (G - 1), base = lane - e;
+    const bool on = e < cnt;
+    const T re = de.w, fce = on ? P.fc(re) : T(0);
+    T z = 0;
+    for (int q = 0; q < most; ++q) {
+        const T qx = __shfl(de.x, base + q, 64), qy = __shfl(de.y, base + q, 64), qz = __shfl(de.z, base + q, 64);
+        const T rq = __shfl(re, base + q, 64), fcq = __shfl(fce, base + q, 64);
+        const T cs = (de.x * qx + de.y * qy + de.z * qz) / (re * rq);
+        T g, dg;
+        P.g_dg(cs, g, dg);
+        if (e != q && q < cnt) z += fcq * g;
+    }
+    T b = T(1), db = T(0), fre = T(0), fae = T(0);
+    if (on) {
+        double b64, fa64;
+        P.bond_order(z, b, db, b64);
+        fre = P.repulsive(re, fce, acc[0]);
+        fae = P.attractive(re, fa64);
+        P.attractive_energy(fce, fae, b, b64, fa64, fre, acc[0]);
+    }
+    const T ire = T(1) / re;
+    const T hx = de.x * ire, hy = de.y * ire, hz = de.z * ire;
+    const T dfce = on ? P.dfc(re) : T(0);
+    const T dV = dfce * (fre - b * fae) + fce * (-P.l1 * fre + b * P.l2 * fae);
+    T px = T(0.5) * dV * hx, py = T(0.5) * dV * hy, pz = T(0.5) * dV * hz;
+    const T pre = fce * fae * db;
+    for (int q = 0; q < most; ++q) {
+        const T qx = __shfl(de.x, base + q, 64), qy = __shfl(de.y, base + q, 64), qz = __shfl(de.z, base + q, 64);
+        const T rq = __shfl(re, base + q, 64), fcq = __shfl(fce, base + q, 64), pre_q = __shfl(pre, base + q, 64);
+        if (e == q || q >= cnt) continue;
+        const T a = T(1) / (re * rq);
+        const T cs = (de.x * qx + de.y * qy + de.z * qz) * a;
+        const T c = cs * ire * ire;
+        const T cx = qx * a - c * de.x, cy = qy * a - c * de.y, cz = qz * a - c * de.z;
+        T g, dg;
+        P.g_dg(cs, g, dg);
+        const T ang = T(0.5) * (pre * fcq + pre_q * fce) * dg;
+        const T rad = T(0.5) * pre_q * dfce * g;
+        px -= ang * cx + rad * hx;
+        py -= ang * cy + rad * hy;
+        pz -= ang * cz + rad * hz;
+    }
+    if (!on) return;
+    store3(Pout, size_t(cid) * N + i, px, py, pz);
+    add_virial<T>(acc, de.x, de.y, de.z, px, py, pz);
+}
+
+// The atoms of `many` (lanes of this wave), 64 / G at a time.
+template <typename T, int G>
+__device__ void ts_crowded(const TersoffT<T>& P, unsigned long long many, int nb, int i, const vec4_t<T>* dv,
+                           const int* bcid, gmem<P3<T>>* Pout, size_t N, double* acc)
+{
+    const int lane = int(threadIdx.x) & 63, e = lane & (G - 1);
+    while (many) {
+        int src = -1;
+#pragma unroll
+        for (int g = 0; g < 64 / G; ++g) {
+            const int s = many ? __ffsll(many) - 1 : -1;
+            many &= many - 1;
+            src = lane / G == g ? s : src;
+        }
+        // (every lane takes part in the exchanges)
+        const int ns = __shfl(nb, max(src, 0), 64), is = __shfl(i, max(src, 0), 64);
+        const int n = src < 0 ? 0 : ns;
+        int most = n;
+        for (int off = 32; off >= G; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
+        most = uni(most);
+        vec4_t<T> d{};
+        d.w = T(1);
+        int cid = 0;
+        if (e < n) {
+            d = dv[size_t(e) * N + is];
+            cid = bcid[size_t(e) * N + is];
+        }
+        ts_atom_group<T, G>(P, d, cid, Pout, N, is, n, most, acc);
+    }
+}
+
+// More bonds than a wave has lanes, one thread: bond orders go through the per-bond scratch
+// array; bcid holds each bond's candidate slot.
 template <typename T>
 __device__ void ts_atom_generic(const TersoffT<T>& P, const vec4_t<T>* dv, vec2_t<T>* bo, const int* bcid,
                                 P3<T>* Pout, size_t N, int i, int cnt, double* acc)
@@ -407,8 +499,27 @@ __device__ void ts_reverse_candidates(const BandDev& b, BandState* st, int slot,
     if (missing) set_error(st, CFNEB_ENEIGH);
 }
 
-// Bonds held in LDS per thread, for atoms with at most this many (carbon: 3 or 4).
-#define TS_LDS_BONDS 4
+
+// A wave's atoms with more than four bonds, after ts_filter_bonds_item: their P to the
+// bonds' candidate slots, their energy and virial added to the wave's partials.
+template <typename T>
+__device__ void ts_many_bonds(const BandDev& b, int slot, int tile)
+{
+    const TersoffT<T> P(b);
+    const size_t N = b.N;
+    const int i = tile * CFNEB_TILE + int(threadIdx.x);
+    P3<T>* Praw = reinterpret_cast<P3<T>*>(b.P) + size_t(slot) * b.ccap * N;
+    const vec4_t<T>* dv = reinterpret_cast<const vec4_t<T>*>(b.dvec) + size_t(slot) * b.cap * N;
+    const int* bcid = reinterpret_cast<const int*>(b.bcid) + size_t(slot) * b.cap * N;
+    const int nb = i < b.N ? b.ncnt[size_t(slot) * N + i] : 0;
+    double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    ts_crowded<T, 8>(P, __ballot(nb > TS_LDS_BONDS && nb <= 8), nb, i, dv, bcid, gp(Praw), N, acc);
+    ts_crowded<T, 64>(P, __ballot(nb > 8 && nb <= 64), nb, i, dv, bcid, gp(Praw), N, acc);
+    if (nb > 64)
+        ts_atom_generic<T>(P, dv, reinterpret_cast<vec2_t<T>*>(b.bo) + size_t(slot) * b.cap * N, bcid, Praw, N, i, nb,
+                           acc);
+    store_ev_partials<true>(b, slot, tile, acc);
+}
 
 // Neighbours of atom i by the exact test of its candidates (as the candidate filter
 // does for LJ), then u_i, P_ij and the per-atom virial from the bond vectors; wave
@@ -417,20 +528,19 @@ __device__ void ts_reverse_candidates(const BandDev& b, BandState* st, int slot,
 // and then to registers; an atom with more bonds writes them to global scratch and
 // takes the general path.
 template <typename T>
-__device__ void ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, int tile,
-                                     vec4_t<T>* lbond, int* lcid)
+__device__ bool ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, int tile, vec4_t<T>* lbond, int* lcid)
 {
     constexpr int MB = TS_LDS_BONDS;
     const int tid = threadIdx.x;
     const int i = tile * CFNEB_TILE + tid;
     const size_t N = b.N;
     double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    int nb = 0;
     if (i < b.N) {
         const cmem<ImageGeom>* g = cp(b.geom + slot);
         const gmem<const R3>* __restrict__ R = gp<const R3>(Rs(b, slot));
         const gmem<const uint4>* __restrict__ cand = gp<const uint4>(reinterpret_cast<const uint4*>(Cs(b, slot)));
-        P3<T>* Praw = reinterpret_cast<P3<T>*>(b.P) + size_t(slot) * b.ccap * N;
-        gmem<P3<T>>* __restrict__ Pout = gp(Praw);
+        gmem<P3<T>>* __restrict__ Pout = gp(reinterpret_cast<P3<T>*>(b.P) + size_t(slot) * b.ccap * N);
         vec4_t<T>* dv = reinterpret_cast<vec4_t<T>*>(b.dvec) + size_t(slot) * b.cap * N;
         int* bcid = reinterpret_cast<int*>(b.bcid) + size_t(slot) * b.cap * N;
         double h[9];
@@ -483,23 +593,30 @@ __device__ void ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
             }
         }
         if (cnt > cap) set_error(st, CFNEB_ENEIGH);
-        const int nb = min(cnt, cap);
-        const TersoffT<T> P(b);
+        nb = min(cnt, cap);
         if (nb <= MB) {
+            const TersoffT<T> P(b);
             vec4_t<T> bond[MB];
 #pragma unroll
             for (int e = 0; e < MB; ++e) bond[e] = (e < nb) ? lbond[e * CFNEB_TILE + tid] : zero;
             ts_atom_regs<T, MB>(P, bond, lcid + tid, CFNEB_TILE, Pout, N, i, nb, acc);
-        } else {
+        }
+    }
+    const bool crowded = __any(nb > MB);  // uniform over the wave
+    if (crowded && i < b.N) {
+        // the wave's counts, and every bond of such atoms, for ts_many_bonds
+        gp(b.ncnt)[size_t(slot) * N + i] = nb;
+        if (nb > MB) {
+            vec4_t<T>* dv = reinterpret_cast<vec4_t<T>*>(b.dvec) + size_t(slot) * b.cap * N;
+            int* bcid = reinterpret_cast<int*>(b.bcid) + size_t(slot) * b.cap * N;
             for (int e = 0; e < MB; ++e) {
                 dv[size_t(e) * N + i] = lbond[e * CFNEB_TILE + tid];
                 bcid[size_t(e) * N + i] = lcid[e * CFNEB_TILE + tid];
             }
-            vec2_t<T>* bo = reinterpret_cast<vec2_t<T>*>(b.bo) + size_t(slot) * b.cap * N;
-            ts_atom_generic<T>(P, dv, bo, bcid, Praw, N, i, nb, acc);
         }
     }
     store_ev_partials(b, slot, tile, acc);
+    return crowded;
 }
 
 template <typename T>
@@ -509,11 +626,24 @@ __device__ void ts_filter_bonds_loop(const BatchDev& bd, int all_images, int var
     __shared__ int lcid[TS_LDS_BONDS * CFNEB_TILE];
     ItemLoopRO loop(bd, KIND_TS, all_images);
     Item it;
-    while (loop.next(it)) {
+    unsigned long long crowded = 0;  // bit n (63: and later ones): this wave of item n
+    for (int n = 0; loop.next(it); n = min(n + 1, 63)) {
         const BandDev b = band_ro(bd, it.band);
         const cmem<BandState>* sr = cp(b.st);
         if (int(band_variant(b) != variant) | int(band_stopped(sr))) continue;  // uniform over the block
-        ts_filter_bonds_item<T>(b, b.st, sr->slot[it.image], it.tile, lbond, lcid);
+        if (ts_filter_bonds_item<T>(b, b.st, sr->slot[it.image], it.tile, lbond, lcid)) crowded |= 1ull << n;
+    }
+    // the atoms with more bonds than the registers take, in a walk of their own: next to the
+    // other bonds their code costs the common path a quarter in registers
+    if (!crowded) return;  // uniform over the wave (no barrier follows)
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // the bonds go between lanes
+    ItemLoopRO again(bd, KIND_TS, all_images);
+    for (int n = 0; again.next(it); n = min(n + 1, 63)) {
+        if (!((crowded >> n) & 1)) continue;
+        const BandDev b = band_ro(bd, it.band);
+        const cmem<BandState>* sr = cp(b.st);
+        if (int(band_variant(b) != variant) | int(band_stopped(sr))) continue;
+        ts_many_bonds<T>(b, sr->slot[it.image], it.tile);
     }
 }
 
