@@ -85,11 +85,11 @@ __device__ inline void atom_gen_force(const DP D, const T (&fr)[3], double (&f)[
 }
 
 // An item is 1024 rows, four per thread (rows tile*1024 + q*256 + thread, so every
-// load is coalesced).  A tile of atom rows only issues all loads of its four rows
-// before any arithmetic; the image's last tile (cell rows, ragged end) first reduces
-// the image's energy and virial, then goes row by row.
+// load is coalesced), all loads of the four rows issued before any arithmetic.  The image's
+// last tile (cell rows, ragged end) has them in flight while it reduces the image's energy
+// and virial, which the cell rows' force needs.
 template <typename T>
-__device__ void dots_item(const BandDev& b, const BandState* st, int k, int tile, double* lds)
+__device__ void dots_item(const BandDev& b, const cmem<BandState>* st, int k, int tile, double* lds)
 {
     constexpr int Q = CFNEB_TILE4 / CFNEB_TILE;
     const int s0 = st->slot[k], sm = st->slot[k - 1], sp = st->slot[k + 1];
@@ -102,22 +102,22 @@ __device__ void dots_item(const BandDev& b, const BandState* st, int k, int tile
     const gmem<const double>* __restrict__ V = gp<const double>(Vs(b, st->vcur, s0));
     const gmem<const T>* __restrict__ F = gp<const T>(reinterpret_cast<const T*>(b.F) + size_t(s0) * slot_rows(b));
     const size_t ld = b.ld;
-    const int r0 = tile * CFNEB_TILE4 + int(threadIdx.x);
+    const int r0 = tile * CFNEB_TILE4 + int(threadIdx.x), last = b.N + 2;
+    double x0[Q][3], xm[Q][3], xp[Q][3], v[Q][3];
+    T fr[Q][3];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t o = size_t(c) * ld + min(r0 + q * CFNEB_TILE, last);  // (F's pad past N is not used)
+            x0[q][c] = X0[o];
+            xm[q][c] = Xm[o];
+            xp[q][c] = Xp[o];
+            v[q][c] = V[o];
+            fr[q][c] = F[o];
+        }
+    const gmem<const double>* D = gp<const double>(b.geom[s0].D);
     if ((tile + 1) * CFNEB_TILE4 <= b.N) {  // uniform over the block
-        double x0[Q][3], xm[Q][3], xp[Q][3], v[Q][3];
-        T fr[Q][3];
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const size_t o = size_t(c) * ld + (r0 + q * CFNEB_TILE);
-                x0[q][c] = X0[o];
-                xm[q][c] = Xm[o];
-                xp[q][c] = Xp[o];
-                v[q][c] = V[o];
-                fr[q][c] = F[o];
-            }
-        const gmem<const double>* D = gp<const double>(b.geom[s0].D);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             double f[3];
@@ -125,23 +125,20 @@ __device__ void dots_item(const BandDev& b, const BandState* st, int k, int tile
             dots_row(a, x0[q], xm[q], xp[q], v[q], f, true);
         }
     } else {
-        // the image's last tile holds its cell rows, whose force needs the image's
-        // energy and virial: this block reduces them first
-        image_reduce_item(b, const_cast<BandState*>(st), s0, lds);
+        image_reduce_item(b, b.st, s0, lds);
         __syncthreads();
+        const gmem<const double>* G = gp<const double>(b.scal[s0].Fcell);
+#pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int r = r0 + q * CFNEB_TILE;
-            if (r >= b.N + 3) break;
-            double x0[3], xm[3], xp[3], v[3], f[3];
-            for (int c = 0; c < 3; ++c) {
-                const size_t o = size_t(c) * ld + r;
-                x0[c] = X0[o];
-                xm[c] = Xm[o];
-                xp[c] = Xp[o];
-                v[c] = V[o];
+            double f[3];
+            if (r < b.N) {
+                atom_gen_force<T>(D, fr[q], f);
+                dots_row(a, x0[q], xm[q], xp[q], v[q], f, true);
+            } else if (r <= last) {
+                for (int c = 0; c < 3; ++c) f[c] = G[3 * (r - b.N) + c];
+                dots_row(a, x0[q], xm[q], xp[q], v[q], f, false);
             }
-            gen_force_row<T>(b, s0, r, f);
-            dots_row(a, x0, xm, xp, v, f, r < b.N);
         }
     }
     // each wave stores its own partials (no block barrier): [image][dot][tile][wave],
@@ -159,12 +156,12 @@ template <typename T>
 __global__ void __launch_bounds__(CFNEB_TILE) k_band_dots(BatchDev bd, unsigned vmask)
 {
     __shared__ double lds[(CFNEB_TILE / 64) * CFNEB_NDOT];
-    ItemLoop loop(bd, KIND_ROW4, 0);
+    ItemLoopRO loop(bd, KIND_ROW4, 0);
     Item it;
     while (loop.next(it)) {
-        const BandDev& b = bd.bands[it.band];
-        if (!((vmask >> band_variant(b)) & 1u) || band_stopped(b.st)) continue;  // uniform
-        dots_item<T>(b, b.st, it.image, it.tile, lds);
+        const BandDev b = band_ro(bd, it.band);
+        if (!((vmask >> band_variant(b)) & 1u) || band_stopped(cp(b.st))) continue;  // uniform
+        dots_item<T>(b, cp(b.st), it.image, it.tile, lds);
     }
 }
 
@@ -172,7 +169,7 @@ __global__ void __launch_bounds__(CFNEB_TILE) k_band_dots(BatchDev bd, unsigned 
 // lane sums every 64th tile partial, then the wave sums its lanes, in a fixed order.
 __global__ void __launch_bounds__(1024) k_band_dots_reduce(BatchDev bd)
 {
-    ItemLoopRO loop(bd, KIND_IMAGE, 0);
+    ItemLoopRO loop(bd, KIND_DIMAGE, 0);
     Item it;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     while (loop.next(it)) {
@@ -222,7 +219,7 @@ __device__ inline void tangent_coeffs(double Hm, double H0, double Hp, double& a
     }
 }
 
-// One block per band: reduce the dot partials, choose tangents and the climbing
+// One block per band: the dots (scalars_reduce: from their partials), tangents and the climbing
 // image, form the projection coefficients and the FIRE proposal.
 __device__ void scalars_item(const BandDev& b, BandState* st)
 {
@@ -231,8 +228,20 @@ __device__ void scalars_item(const BandDev& b, BandState* st)
     __shared__ double contrib[3][CFNEB_MAX_IMAGES];
     __shared__ int ci_s;
     const int M = st->M;
-    for (int e = threadIdx.x; e < (M - 2) * CFNEB_NDOT; e += int(blockDim.x))
-        dots[1 + e / CFNEB_NDOT][e % CFNEB_NDOT] = b.dotred[CFNEB_NDOT + size_t(e)];
+    if (scalars_reduce(b)) {
+        // sixteen lanes to a sum, in a fixed order
+        const int parts = b.ntR4 * CFNEB_WAVES, lane = int(threadIdx.x) & 15;
+        const gmem<const double>* part = gp<const double>(b.dotpart + size_t(CFNEB_NDOT) * parts);
+        for (int e = int(threadIdx.x) >> 4; e < (M - 2) * CFNEB_NDOT; e += 64) {
+            double a = 0.0;
+            for (int p = lane; p < parts; p += 16) a += part[size_t(e) * parts + p];
+            a = lanes_sum<16>(a);
+            if (lane == 0) dots[1 + e / CFNEB_NDOT][e % CFNEB_NDOT] = a;
+        }
+    } else {
+        for (int e = threadIdx.x; e < (M - 2) * CFNEB_NDOT; e += int(blockDim.x))
+            dots[1 + e / CFNEB_NDOT][e % CFNEB_NDOT] = b.dotred[CFNEB_NDOT + size_t(e)];
+    }
     // image enthalpies, loaded in parallel
     const int t = threadIdx.x;
     if (t < M) H[t] = b.scal[st->slot[t]].H;
@@ -784,7 +793,7 @@ void launch_dots(const Launch& L, hipStream_t s)
     const unsigned g = L.g[KIND_ROW4];
     if (f32_mask(L.variants)) k_band_dots<float><<<g, CFNEB_TILE, 0, s>>>(L.bd, f32_mask(L.variants));
     if (f64_mask(L.variants)) k_band_dots<double><<<g, CFNEB_TILE, 0, s>>>(L.bd, f64_mask(L.variants));
-    k_band_dots_reduce<<<L.g[KIND_IMAGE], 1024, 0, s>>>(L.bd);
+    if (L.variants & (1u << VARIANT_DOTS_REDUCE)) k_band_dots_reduce<<<L.g[KIND_DIMAGE], 1024, 0, s>>>(L.bd);
 }
 
 // Energy profile after an evaluation of every image (launch_evaluate(L, 1, s)).

@@ -375,6 +375,7 @@ enum ItemKind {
     KIND_ATOM4,     // 1024-atom tiles x images (4 atoms per thread), large bands
     KIND_LATOM,     // 256-atom tiles x images, large bands (more than CFNEB_SKIN_IMAGE atoms)
     KIND_LIMAGE,    // one item per image, large bands
+    KIND_DIMAGE,    // one item per image, bands whose dots have a reduction of their own
     KIND_SIMAGE,    // one item per image, the other bands
     KIND_ROW4,      // 1024-row tiles x images (4 rows per thread)
     // items of the energy-forming force kernels (ntF) x images, each kind holding only
@@ -409,6 +410,13 @@ struct Item {
     int band, tile, image;
 };
 
+// Bands with few dot partials: the scalars kernel sums them itself (sixteen lanes to a
+// sum, a round of loads per 64 sums), a launch of 4.6 us less a step.  616 partials (255
+// atoms, 5 images) cost it 0.7 us; 10,560 (4,608 atoms, 22 images) 4.3 us, no gain.
+__host__ __device__ inline bool scalars_reduce(const BandDev& b)
+{
+    return (long long)b.Mcap * CFNEB_NDOT * b.ntR4 * CFNEB_WAVES <= 4096;
+}
 __host__ __device__ inline bool skin_by_image(const BandDev& b) { return b.N <= CFNEB_SKIN_IMAGE; }
 
 __device__ inline int kind_tiles(const BandDev& b, int kind)
@@ -418,6 +426,7 @@ __device__ inline int kind_tiles(const BandDev& b, int kind)
     case KIND_ATOM4: return skin_by_image(b) ? 0 : (b.N + CFNEB_TILE4 - 1) / CFNEB_TILE4;
     case KIND_LATOM: return skin_by_image(b) ? 0 : b.ntA;
     case KIND_LIMAGE: return skin_by_image(b) ? 0 : 1;
+    case KIND_DIMAGE: return scalars_reduce(b) ? 0 : 1;
     case KIND_SIMAGE: return skin_by_image(b) ? 1 : 0;
     case KIND_ROW4: return b.ntR4;
     case KIND_LJ1: return b.potential == CFNEB_LJ && b.lj_lanes == 1 ? b.ntF : 0;
@@ -530,10 +539,12 @@ __device__ inline void plan_block(const BatchDev& bd, int all_images, int ignore
         int c[NKIND];
         for (int q = 0; q < NKIND; ++q) c[q] = 0;
         if (bd.live[t]) {
-            const BandDev& b = bd.bands[t];
-            const BandState* st = b.st;
+            // (nothing here changes while the plan is written)
+            const BandDev b = band_ro(bd, t);
+            const cmem<BandState>* st = cp(b.st);
+            const int M = st->M;
             if (ignore_stop || !band_stopped(st)) {
-                const int M = st->M;
+#pragma unroll
                 for (int q = 0; q < NKIND; ++q) {
                     int first;
                     kind_span(b, q, M, all_images, c[q], first);
@@ -585,10 +596,13 @@ __host__ __device__ inline unsigned lanes_bit(const BandDev& b)
     return b.lj_lanes == 1 ? 1u << 8 : 1u << 9;
 }
 // Bits 10 and 11: bands whose skin test takes one block per image, and larger ones.
-enum { VARIANT_SKIN_IMAGE = 10, VARIANT_SKIN_LARGE };
+// Bit 12: bands whose dots have a reduction of their own.
+enum { VARIANT_SKIN_IMAGE = 10, VARIANT_SKIN_LARGE, VARIANT_DOTS_REDUCE };
 __host__ __device__ inline unsigned launch_variants(const BandDev& b)
 {
-    return (1u << band_variant(b)) | lanes_bit(b) | (1u << (skin_by_image(b) ? VARIANT_SKIN_IMAGE : VARIANT_SKIN_LARGE));
+    return (1u << band_variant(b)) | lanes_bit(b) |
+           (1u << (skin_by_image(b) ? VARIANT_SKIN_IMAGE : VARIANT_SKIN_LARGE)) |
+           (scalars_reduce(b) ? 0u : 1u << VARIANT_DOTS_REDUCE);
 }
 
 // Launch geometry of one batch: the grid of each kind, bounded by the most items
@@ -968,12 +982,20 @@ __device__ inline void store_ev_partials(const BandDev& b, int slot, int tile, c
 __device__ inline void image_reduce_item(const BandDev& b, BandState* st, int slot, double* lds)
 {
     double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    const double* part = b.evpart + size_t(slot) * b.ntF * CFNEB_WAVES * 10;
+    const gmem<const double>* part = gp<const double>(b.evpart + size_t(slot) * b.ntF * CFNEB_WAVES * 10);
+    const cmem<ImageGeom>* gc = cp(b.geom + slot);  // asked for before the sums
+    struct {
+        double D[9], Dinv[9], omega;
+    } g;
+    for (int q = 0; q < 9; ++q) {
+        g.D[q] = gc->D[q];
+        g.Dinv[q] = gc->Dinv[q];
+    }
+    g.omega = gc->omega;
     for (int t = threadIdx.x; t < b.ntF * CFNEB_WAVES; t += CFNEB_TILE)
         for (int q = 0; q < 10; ++q) acc[q] += part[size_t(t) * 10 + q];
     block_sum<10>(acc, lds);
     if (threadIdx.x != 0) return;
-    const ImageGeom& g = b.geom[slot];
     ImageScal& s = b.scal[slot];
     s.E = acc[0];
     s.H = acc[0] + b.press * g.omega;

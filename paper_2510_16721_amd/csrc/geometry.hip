@@ -62,12 +62,12 @@ __device__ __forceinline__ bool sym_sqrt(const double* Bin, double* D)
     return true;
 }
 
-__device__ __forceinline__ bool image_geometry(const BandDev& b, const double* X, ImageGeom& g)
+// Geometry from the cell rows of X (row-major).
+__device__ __forceinline__ bool image_geometry(const BandDev& b, const double (&rows)[9], ImageGeom& g)
 {
     double B[9];
     const double icf = 1.0 / b.cf;
-    for (int q = 0; q < 3; ++q)
-        for (int c = 0; c < 3; ++c) B[3 * q + c] = X[size_t(c) * b.ld + b.N + q] * icf;
+    for (int q = 0; q < 9; ++q) B[q] = rows[q] * icf;
     if (b.cell_filter == 1) {
         // D-variant: the cell rows hold c_f D itself (rotations included)
         for (int q = 0; q < 9; ++q) g.D[q] = B[q];
@@ -160,34 +160,47 @@ __device__ __forceinline__ void fixed_point_bounds(const BandDev& b, ImageGeom& 
 }
 
 // Geometry of image k of band b and its strain since the candidate build; in a step,
-// first the pending move of the image's cell rows.
-__device__ __forceinline__ void geom_image(const BandDev& b, BandState* st, int k, int all_images)
+// first the pending move of the image's cell rows.  A chain of dependent loads and FP64
+// operations in a few lanes: everything it reads is asked for at once (the band state's
+// fields read here are not written by this kernel).
+__device__ __forceinline__ void geom_image(const BandDev& b, const cmem<BandState>* sr, int k, int all_images)
 {
-    // the band state's fields read here are not written by this kernel
-    const cmem<BandState>* sr = cp(st);
     const int slot = sr->slot[k];
-    if (move_pending(sr, all_images)) {
-        gmem<double>* X = gp(Xs(b, slot));
-        const gmem<const double>* V = gp<const double>(Vs(b, sr->vcur, slot));
-        const double sc = sr->scale, dt = sr->dt;
+    gmem<double>* X = gp(Xs(b, slot));
+    const gmem<const double>* V = gp<const double>(Vs(b, sr->vcur, slot));
+    const cmem<SkinState>* sk = cp(b.skst + slot);
+    const bool move = move_pending(sr, all_images);
+    const double sc = sr->scale, dt = sr->dt;
+    double rows[9], v[9], hri[9];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t o = size_t(c) * b.ld + b.N + q;
+            rows[3 * q + c] = X[o];
+            v[3 * q + c] = V[o];
+        }
+    const bool valid = sk->valid != 0;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) hri[q] = sk->hrefinv[q];
+    if (move) {
+#pragma unroll
         for (int q = 0; q < 3; ++q)
+#pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const size_t o = size_t(c) * b.ld + b.N + q;
-                X[o] += sc * (dt * V[o]);
+                rows[3 * q + c] += sc * (dt * v[3 * q + c]);
+                X[size_t(c) * b.ld + b.N + q] = rows[3 * q + c];
             }
     }
     ImageGeom g;
     g.err = 0;
-    if (!image_geometry(b, Xs(b, slot), g)) {
+    if (!image_geometry(b, rows, g)) {
         g.err = 1;
-        set_error(st, CFNEB_ECELL);
+        set_error(b.st, CFNEB_ECELL);
     }
     // strain since the candidate build: E = h_ref^-1 h - I
-    const cmem<SkinState>& sk = *cp(b.skst + slot);
     g.enorm = 0.0;
-    if (sk.valid) {
-        double hri[9];
-        for (int q = 0; q < 9; ++q) hri[q] = sk.hrefinv[q];
+    if (valid) {
         mm3(hri, g.h, g.E);
         for (int q = 0; q < 3; ++q) g.E[4 * q] -= 1.0;
         for (int q = 0; q < 9; ++q) g.enorm += g.E[q] * g.E[q];
@@ -211,11 +224,11 @@ __global__ void __launch_bounds__(CFNEB_MAX_BANDS) k_geom(BatchDev bd, int all_i
     }
     for (int t = int(blockIdx.x) - 1; t < bd.cap; t += int(gridDim.x) - 1) {
         if (!bd.live[t]) continue;
-        const BandDev& b = bd.bands[t];
-        BandState* st = b.st;
-        const int k = threadIdx.x;
-        if (band_stopped(st) || k >= b.Mcap || !image_active(st, k, all_images)) continue;
-        geom_image(b, st, k, all_images);
+        const BandDev b = band_ro(bd, t);
+        const cmem<BandState>* sr = cp(b.st);
+        const int k = threadIdx.x, M = sr->M;
+        if (int(band_stopped(sr)) | int(k < (all_images ? 0 : 1)) | int(k >= (all_images ? M : M - 1))) continue;
+        geom_image(b, sr, k, all_images);
     }
 }
 
@@ -320,7 +333,10 @@ __global__ void k_image_geom_one(BandDev b, int k)
     BandState* st = b.st;
     if (k < 0 || k >= st->M) return;
     ImageGeom g;
-    const bool ok = image_geometry(b, Xs(b, st->slot[k]), g);
+    double rows[9];
+    const double* X = Xs(b, st->slot[k]);
+    for (int q = 0; q < 9; ++q) rows[q] = X[size_t(q % 3) * b.ld + b.N + q / 3];
+    const bool ok = image_geometry(b, rows, g);
     double* out = b.staging + 3 * size_t(b.N);
     for (int q = 0; q < 9; ++q) out[q] = ok ? g.h[q] : 0.0;
     for (int q = 0; q < 9; ++q) out[9 + q] = ok ? g.D[q] : 0.0;
