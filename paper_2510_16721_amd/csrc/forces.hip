@@ -164,6 +164,11 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
 // rounding error, a strain of ~1e-7 that the virial sum multiplies by the stiffness).
 // The FP32 r^2 settles the pair outside [r2lo, r2hi); inside that band the exact FP64
 // test runs on the FP64 positions.
+// Bound by two units at once (97,555 atoms x 22 images, 8 % under either): 57 vector
+// instructions a pair fill 92 % of the issue slots, the position gathers take 91 % of the
+// cache's cycles (a lane's line each).  The next four entries load during this batch, and a
+// pair outside rc is dropped by one select: 341 -> 338 us there; in a batch of 64 bands of
+// up to 32,000 atoms 224 -> 206 us a step here and 202 -> 180 us with several lanes.
 // Loads at a 32-bit byte offset from a uniform base (one address add per load).
 __device__ inline uint4 ld_u128(const void* base, uint32_t off)
 {
@@ -215,12 +220,16 @@ __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int til
         // the wave's atoms share one block of 64: a uniform base and a 32-bit offset
         const uint32_t* block = uni(cand + size_t(i >> 6) * cand_block(ccap));
         uint32_t off = (uint32_t(lane) * 64u + uint32_t(i & 63)) * 16u;
-        for (int e0 = U * lane; e0 < nc; e0 += U * K, off += uint32_t(K) * 1024u) {
-            const uint4 four = ld_u128(block, off);
+        uint4 next = nc > U * lane ? ld_u128(block, off) : make_uint4(0u, 0u, 0u, 0u);
+        for (int e0 = U * lane; e0 < nc; e0 += U * K) {
+            // the next entries are in flight during this batch (the last asks for its own)
+            const uint4 four = next;
+            off += e0 + U * K < nc ? uint32_t(K) * 1024u : 0u;
             const uint32_t ent[U] = {four.x, four.y, four.z, four.w};
             uint4 sj[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) sj[u] = ld_u96(S, uint32_t(nbr_j(ent[u])) * 12u);
+            next = ld_u128(block, off);
             __builtin_amdgcn_sched_barrier(0);
             float w[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             const int cnt0 = cnt;
@@ -233,24 +242,24 @@ __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int til
                 const float dy = float(a0 * H[1] + a1 * H[4] + a2 * H[7]);
                 const float dz = float(a0 * H[2] + a1 * H[5] + a2 * H[8]);
                 const float r2 = dx * dx + dy * dy + dz * dz;
-                const bool valid = e0 + u < nc;
-                bool inside = valid && r2 < lo;
-                if (valid && r2 >= lo && r2 < hi) {  // rare: the exact FP64 test on the FP64 positions
+                const bool valid = e0 + u < nc, below = r2 < lo;
+                bool inside = valid & below;
+                if (valid & (r2 < hi) & !below) {  // rare: the exact FP64 test on the FP64 positions
                     const double4 r4 = load4(R, ii);
                     const double ri[3] = {r4.x, r4.y, r4.z};
                     double d[3];
                     separation(ri, load4(R, nbr_j(ent[u])), h, ent[u], d);
                     inside = exact_r2(d) < rc2;
                 }
-                // every lane takes the pair arithmetic; pairs outside rc add zeros.  The
-                // terms are in units of 24 eps (force) and 4 eps (energy, before the
-                // shift): the constants multiply the sums
-                const float ir2 = __builtin_amdgcn_rcpf(r2);
+                // every lane takes the pair arithmetic; pairs outside rc (1 / r^2 taken as 0)
+                // add zeros.  The terms are in units of 24 eps (force) and 4 eps (energy,
+                // before the shift): the constants multiply the sums
+                const float ir2 = inside ? __builtin_amdgcn_rcpf(r2) : 0.f;
                 float s6 = sig2 * ir2;
                 s6 = s6 * s6 * s6;
                 const float s12 = s6 * s6;
-                const float fr = inside ? (s6 - 2.f * s12) * ir2 : 0.f;  // phi'(r) / (24 eps r)
-                const float phi = inside ? s12 - s6 : 0.f;               // (phi(r) + shift) / (4 eps)
+                const float fr = (s6 - 2.f * s12) * ir2;  // phi'(r) / (24 eps r)
+                const float phi = s12 - s6;               // (phi(r) + shift) / (4 eps)
                 cnt += inside ? 1 : 0;
                 const float px = fr * dx, py = fr * dy, pz = fr * dz;
                 fx += px;
@@ -300,9 +309,10 @@ __device__ __forceinline__ void lj_item(const BandDev& b, BandState* st, int slo
     lj_cand_item<T, K>(b, st, slot, tile);
 }
 
-// Bands of one lane per atom (the large ones).
+// Bands of one lane per atom (the large ones).  Four waves per SIMD without a spill: five
+// with one ran 346 us where four run 338 (97,555 atoms x 22 images, FP32).
 template <typename T>
-__device__ void lj_one_loop(const BatchDev& bd, int all_images, int variant)
+__global__ void __launch_bounds__(CFNEB_TILE) k_lj_one(BatchDev bd, int all_images, int variant)
 {
     ItemLoopRO loop(bd, KIND_LJ1, all_images);
     Item it;
@@ -312,22 +322,6 @@ __device__ void lj_one_loop(const BatchDev& bd, int all_images, int variant)
         if (int(band_variant(b) != variant) | int(band_stopped(sr))) continue;  // uniform over the block
         lj_item<T, 1>(b, b.st, sr->slot[it.image], it.tile);
     }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(CFNEB_TILE) k_lj_one(BatchDev bd, int all_images, int variant)
-{
-    lj_one_loop<T>(bd, all_images, variant);
-}
-
-// FP32, one lane per atom: five waves per SIMD at a small spill run faster than four
-// without one (force kernel 391 -> 365 us on the 97,555-atom band); with several lanes
-// the kernel keeps its registers (it would spill 20-24 dwords at five).
-template <>
-__global__ void __launch_bounds__(CFNEB_TILE) __attribute__((amdgpu_waves_per_eu(5)))
-k_lj_one<float>(BatchDev bd, int all_images, int variant)
-{
-    lj_one_loop<float>(bd, all_images, variant);
 }
 
 // Bands of several lanes per atom: every count in one launch (a launch per count leaves
