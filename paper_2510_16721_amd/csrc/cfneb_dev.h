@@ -43,10 +43,18 @@
 #define CFNEB_TILE_CAND 128
 #define CFNEB_TILE4 1024         // rows (atoms) of a streaming item with 4 per thread
 // Bands of up to this many atoms have their positions, skin test and bins done by one
-// block per image (k_skin_image) instead of six launches (4,608 atoms: 15 against 24 us a
-// step; a block needs 4 us per further 4,096 atoms, the launches' fixed part is 20 us).
-// Above, the bins would not fit in LDS.
-#define CFNEB_SKIN_IMAGE 8192
+// block per image (k_skin_image) instead of two launches or six.  The line is one round of
+// the block's 1,024 threads at four atoms each: 2,047 atoms x 18 images take 10.6 us a step
+// so and 14 us in two launches; 4,608 atoms x 22 images 17.6 us so and 15.9 us in two.
+#define CFNEB_SKIN_IMAGE 4096
+// Up to this many the decision and the bins take one launch, a block per image
+// (k_skin_bins), instead of five of which four idle on most steps: 16,383 atoms x 9 images
+// 27 -> 12 us a step (38 us instead of 55 when an image rebuilds), 64 bands of up to 32,000
+// atoms 101 -> 60 us.  A block's time grows with the atoms while the launches spread over the
+// chip: at 37,000 atoms x 22 images a step without a rebuild is 11 us faster so and one with
+// a rebuild 18 us slower, even where four steps in ten rebuild (carbon: one in twenty or
+// less, 4 % faster; LJ in its first hundred steps: even).
+#define CFNEB_BIN_IMAGE 36864
 #define CFNEB_WAVES 4            // waves per block of CFNEB_TILE threads
 #define CFNEB_NDOT 22            // band-dot partial sums per moving image and row tile
 #define CFNEB_NPROF 14           // energy-profile partial sums per image and row tile
@@ -372,11 +380,12 @@ enum ItemKind {
     KIND_IVAL,      // 256-row tiles x intervals between consecutive images
     KIND_SLOTROW,   // 256-row tiles x every image slot of the capacity
     KIND_BAND,      // one item per band
-    KIND_ATOM4,     // 1024-atom tiles x images (4 atoms per thread), large bands
-    KIND_LATOM,     // 256-atom tiles x images, large bands (more than CFNEB_SKIN_IMAGE atoms)
+    KIND_ATOM4,     // 1024-atom tiles x images (4 atoms per thread), more than CFNEB_SKIN_IMAGE atoms
+    KIND_LATOM,     // 256-atom tiles x images, large bands (more than CFNEB_BIN_IMAGE atoms)
     KIND_LIMAGE,    // one item per image, large bands
+    KIND_BIMAGE,    // one item per image, bands between the two
     KIND_DIMAGE,    // one item per image, bands whose dots have a reduction of their own
-    KIND_SIMAGE,    // one item per image, the other bands
+    KIND_SIMAGE,    // one item per image, up to CFNEB_SKIN_IMAGE atoms
     KIND_ROW4,      // 1024-row tiles x images (4 rows per thread)
     // items of the energy-forming force kernels (ntF) x images, each kind holding only
     // the bands that its kernel serves (a kernel that walks the items of other bands to
@@ -418,14 +427,17 @@ __host__ __device__ inline bool scalars_reduce(const BandDev& b)
     return (long long)b.Mcap * CFNEB_NDOT * b.ntR4 * CFNEB_WAVES <= 4096;
 }
 __host__ __device__ inline bool skin_by_image(const BandDev& b) { return b.N <= CFNEB_SKIN_IMAGE; }
+__host__ __device__ inline bool bins_by_tiles(const BandDev& b) { return b.N > CFNEB_BIN_IMAGE; }
+__host__ __device__ inline bool bins_by_image(const BandDev& b) { return !skin_by_image(b) && !bins_by_tiles(b); }
 
 __device__ inline int kind_tiles(const BandDev& b, int kind)
 {
     switch (kind) {
     case KIND_ATOM: return b.ntA;
     case KIND_ATOM4: return skin_by_image(b) ? 0 : (b.N + CFNEB_TILE4 - 1) / CFNEB_TILE4;
-    case KIND_LATOM: return skin_by_image(b) ? 0 : b.ntA;
-    case KIND_LIMAGE: return skin_by_image(b) ? 0 : 1;
+    case KIND_LATOM: return bins_by_tiles(b) ? b.ntA : 0;
+    case KIND_LIMAGE: return bins_by_tiles(b) ? 1 : 0;
+    case KIND_BIMAGE: return bins_by_image(b) ? 1 : 0;
     case KIND_DIMAGE: return scalars_reduce(b) ? 0 : 1;
     case KIND_SIMAGE: return skin_by_image(b) ? 1 : 0;
     case KIND_ROW4: return b.ntR4;
@@ -433,7 +445,7 @@ __device__ inline int kind_tiles(const BandDev& b, int kind)
     case KIND_LJK: return b.potential == CFNEB_LJ && b.lj_lanes > 1 ? b.ntF : 0;
     case KIND_TS: return b.potential == CFNEB_TERSOFF_C ? b.ntF : 0;
     case KIND_CAND: return (b.N + CFNEB_TILE_CAND - 1) / CFNEB_TILE_CAND;
-    case KIND_BIN: return skin_by_image(b) ? 0 : (b.nbcap + CFNEB_TILE - 1) / CFNEB_TILE;
+    case KIND_BIN: return bins_by_tiles(b) ? (b.nbcap + CFNEB_TILE - 1) / CFNEB_TILE : 0;
     case KIND_ROW:
     case KIND_IVAL:
     case KIND_SLOTROW: return b.ntR;
@@ -595,13 +607,13 @@ __host__ __device__ inline unsigned lanes_bit(const BandDev& b)
     if (b.potential != CFNEB_LJ) return 0u;
     return b.lj_lanes == 1 ? 1u << 8 : 1u << 9;
 }
-// Bits 10 and 11: bands whose skin test takes one block per image, and larger ones.
-// Bit 12: bands whose dots have a reduction of their own.
-enum { VARIANT_SKIN_IMAGE = 10, VARIANT_SKIN_LARGE, VARIANT_DOTS_REDUCE };
+// Bits 10 to 12: bands whose skin test and bins take one block per image, those whose bins
+// do, and larger ones.  Bit 13: bands whose dots have a reduction of their own.
+enum { VARIANT_SKIN_IMAGE = 10, VARIANT_BIN_IMAGE, VARIANT_BIN_TILES, VARIANT_DOTS_REDUCE };
 __host__ __device__ inline unsigned launch_variants(const BandDev& b)
 {
     return (1u << band_variant(b)) | lanes_bit(b) |
-           (1u << (skin_by_image(b) ? VARIANT_SKIN_IMAGE : VARIANT_SKIN_LARGE)) |
+           (1u << (skin_by_image(b) ? VARIANT_SKIN_IMAGE : bins_by_image(b) ? VARIANT_BIN_IMAGE : VARIANT_BIN_TILES)) |
            (scalars_reduce(b) ? 0u : 1u << VARIANT_DOTS_REDUCE);
 }
 

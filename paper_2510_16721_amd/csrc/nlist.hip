@@ -15,7 +15,8 @@
 // against it is within 2^-24 |R_ref,i| (1 + |E|) of the true one, added to the bound.
 //
 // Kernels, in order (each a persistent walk over the items of every live band); bands of
-// up to CFNEB_SKIN_IMAGE atoms take k_skin_image instead of all before k_cand:
+// up to CFNEB_SKIN_IMAGE atoms take k_skin_image instead of all before k_cand, those of up
+// to CFNEB_BIN_IMAGE k_skin_bins instead of k_skin_decide and the four bin kernels:
 //   k_skin_check   (steps) the previous step's move of the atom rows; R = R~ D (and
 //                  its fixed-point fractional coordinates); max_i d_i^2 per 1024-atom tile
 //   k_skin_decide  max over an image's tiles, rebuild flag per image; a rebuild takes
@@ -221,7 +222,7 @@ __global__ void __launch_bounds__(16 * CFNEB_MAX_IMAGES) k_skin_decide(BatchDev 
     Item it;
     while (loop.next(it)) {
         const BandDev& b = bd.bands[it.band];
-        if (skin_by_image(b)) continue;
+        if (!bins_by_tiles(b)) continue;
         const BandState* st = b.st;
         const int k = threadIdx.x >> 4, lane = threadIdx.x & 15;
         const bool act = !band_stopped(st) && k < b.Mcap && image_active(st, k, all_images);
@@ -281,20 +282,112 @@ __device__ inline BinAtom bin_record(const ImageGeom& g, const double4& ri, int 
     return a;
 }
 
+// The bins of one image by one block of 1024 threads: counts, then starts, and the ids of
+// each bin in LDS (16 bits each: at most CFNEB_BIN_IMAGE atoms).  Four atoms a thread at a
+// time, so the loads of a round are in flight together.
+__device__ void bins_of_image(const BandDev& b, const ImageGeom& g, int slot, unsigned short* start,
+                              unsigned short* ids, int* wsum)
+{
+    constexpr int Q = 4;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int N = b.N, nbins = g.nbins;
+    unsigned* counts = reinterpret_cast<unsigned*>(start);  // two bins to a word
+    for (int q = t; q <= nbins / 2; q += 1024) counts[q] = 0;
+    __syncthreads();
+    gmem<int>* __restrict__ info = gp(b.binfo + size_t(slot) * 3 * N);
+    const gmem<const R3>* __restrict__ R = gp<const R3>(Rs(b, slot));
+    for (int i0 = t; i0 < N; i0 += 1024 * Q) {
+        double4 r[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) r[q] = load4(R, min(i0 + 1024 * q, N - 1));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = i0 + 1024 * q;
+            if (i >= N) break;
+            int img[3];
+            const int bin = bin_of(g, r[q], img), sh = (bin & 1) * 16;
+            info[i] = bin;
+            info[N + i] = int((atomicAdd(&counts[bin >> 1], 1u << sh) >> sh) & 0xFFFFu);
+            info[2 * N + i] = pack_binfo_image(img);
+            if (image_is_far(img)) b.skst[slot].far = 1;
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the counts, a run of bins per thread
+    const int per = (nbins + 1023) >> 10, q0 = min(t * per, nbins), q1 = min(q0 + per, nbins);
+    int sum = 0;
+    for (int q = q0; q < q1; ++q) sum += start[q];
+    int incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += y;
+    }
+    if (lane == 63) wsum[wid] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int w = 0; w < wid; ++w) run += wsum[w];
+    gmem<int>* __restrict__ gstart = gp(b.bstart + bin_base(b, slot));
+    for (int q = q0; q < q1; ++q) {
+        const int c = start[q];
+        start[q] = (unsigned short)run;
+        gstart[q] = run;
+        run += c;
+    }
+    if (t == 0) {
+        start[nbins] = (unsigned short)N;
+        gstart[nbins] = N;
+    }
+    __syncthreads();
+    for (int i0 = t; i0 < N; i0 += 1024 * Q) {
+        int bin[Q], rank[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = min(i0 + 1024 * q, N - 1);
+            bin[q] = info[i];
+            rank[q] = info[N + i];
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (i0 + 1024 * q < N) ids[int(start[bin[q]]) + rank[q]] = (unsigned short)(i0 + 1024 * q);
+    }
+    __syncthreads();
+    // an atom's place in its bin is the number of smaller ids there
+    BinAtom* out = b.bpos + size_t(slot) * N;
+    for (int i0 = t; i0 < N; i0 += 1024 * Q) {
+        int bin[Q], im[Q];
+        double4 r[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = min(i0 + 1024 * q, N - 1);
+            bin[q] = info[i];
+            im[q] = info[2 * N + i];
+            r[q] = load4(R, i);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = i0 + 1024 * q;
+            if (i >= N) break;
+            const int lo = start[bin[q]], hi = start[bin[q] + 1];
+            int pos = lo;
+            for (int p = lo; p < hi; ++p) pos += int(ids[p]) < i ? 1 : 0;
+            out[pos] = bin_record(g, r[q], i, im[q]);
+        }
+    }
+    __syncthreads();
+}
+
 // Bands of up to CFNEB_SKIN_IMAGE atoms: one block per image takes the positions, the skin
-// test, the decision and, on a rebuild, the bins in bin order, sorted by id: counts, starts
-// and the atoms of each bin are in LDS, so the phases that are launches of their own for
-// large bands (four of them idle on most steps) are block barriers here.  Latency-bound.
-// Skin test and idle bin launches per step: 4,608 carbon atoms x 22 images 24 -> 15 us,
-// 255 LJ atoms x 5 images 15 -> 7 us.
+// test, the decision and, on a rebuild, the bins, so the phases that are launches of their
+// own for large bands (four of them idle on most steps) are block barriers here.
+// Latency-bound.  Skin test and idle bin launches per step: 255 LJ atoms x 5 images 15 -> 7 us.
 __global__ void __launch_bounds__(1024) k_skin_image(BatchDev bd, int all_images)
 {
     __shared__ double lds[16 * 2];
-    __shared__ int start[CFNEB_SKIN_IMAGE + 64 + 1];
+    __shared__ alignas(4) unsigned short start[CFNEB_SKIN_IMAGE + 64 + 2];
     __shared__ unsigned short ids[CFNEB_SKIN_IMAGE];
     __shared__ int wsum[16];
     __shared__ int rebuild;
-    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int t = threadIdx.x;
     ItemLoopRO loop(bd, KIND_SIMAGE, all_images);
     Item it;
     while (loop.next(it)) {
@@ -311,55 +404,45 @@ __global__ void __launch_bounds__(1024) k_skin_image(BatchDev bd, int all_images
         if (t == 0) rebuild = skin_decision(bd, b, slot, m) ? 1 : 0;
         __syncthreads();
         if (!rebuild) continue;  // uniform (the next write of the flag is behind barriers)
-        const ImageGeom& g = b.geom[slot];
-        const int nbins = g.nbins;
-        for (int q = t; q <= nbins; q += 1024) start[q] = 0;
-        __syncthreads();
-        int* info = b.binfo + size_t(slot) * 3 * N;
-        const gmem<const R3>* R = gp<const R3>(Rs(b, slot));
-        for (int i = t; i < N; i += 1024) {
-            int img[3];
-            const int bin = bin_of(g, load4(R, i), img);
-            info[i] = bin;
-            info[N + i] = atomicAdd(&start[bin], 1);
-            info[2 * N + i] = pack_binfo_image(img);
-            if (image_is_far(img)) b.skst[slot].far = 1;
+        bins_of_image(b, b.geom[slot], slot, start, ids, wsum);
+    }
+}
+
+// Bands of up to CFNEB_BIN_IMAGE atoms: one block per image takes the decision from the
+// tiles' maxima (as k_skin_decide) and, on a rebuild, the bins.  Bound by launches when no
+// image rebuilds, by one CU's round trips when one does (figures at CFNEB_BIN_IMAGE).
+__global__ void __launch_bounds__(1024) k_skin_bins(BatchDev bd, int all_images)
+{
+    __shared__ alignas(4) unsigned short start[CFNEB_BIN_IMAGE + 64 + 2];
+    __shared__ unsigned short ids[CFNEB_BIN_IMAGE];
+    __shared__ int wsum[16];
+    __shared__ int rebuild;
+    ItemLoopRO loop(bd, KIND_BIMAGE, all_images);
+    Item it;
+    while (loop.next(it)) {
+        const BandDev b = band_ro(bd, it.band);
+        const cmem<BandState>* st = cp(b.st);
+        if (band_stopped(st)) continue;  // uniform over the block
+        const int slot = st->slot[it.image];
+        if (threadIdx.x < 64) {
+            const int nt = kind_tiles(b, KIND_ATOM4);
+            const gmem<const double>* mx = gp<const double>(b.skmax + size_t(slot) * nt * 2);
+            double m[2] = {0.0, 0.0};
+            for (int k = threadIdx.x; k < nt; k += 64) {
+                m[0] = fmax(m[0], mx[2 * k]);
+                m[1] = fmax(m[1], mx[2 * k + 1]);
+            }
+            for (int off = 32; off > 0; off >>= 1) {
+                m[0] = fmax(m[0], __shfl_xor(m[0], off, 64));
+                m[1] = fmax(m[1], __shfl_xor(m[1], off, 64));
+            }
+            if (threadIdx.x == 0) rebuild = skin_decision(bd, b, slot, m) ? 1 : 0;
         }
         __syncthreads();
-        // exclusive scan of the counts, a run of bins per thread
-        const int per = (nbins + 1023) >> 10, q0 = min(t * per, nbins), q1 = min(q0 + per, nbins);
-        int sum = 0;
-        for (int q = q0; q < q1; ++q) sum += start[q];
-        int incl = sum;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int y = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += y;
-        }
-        if (lane == 63) wsum[wid] = incl;
-        __syncthreads();
-        int run = incl - sum;
-        for (int w = 0; w < wid; ++w) run += wsum[w];
-        int* gstart = b.bstart + bin_base(b, slot);
-        for (int q = q0; q < q1; ++q) {
-            const int c = start[q];
-            start[q] = run;
-            gstart[q] = run;
-            run += c;
-        }
-        if (t == 0) {
-            start[nbins] = N;
-            gstart[nbins] = N;
-        }
-        __syncthreads();
-        for (int i = t; i < N; i += 1024) ids[start[info[i]] + info[N + i]] = (unsigned short)i;
-        __syncthreads();
-        // an atom's place in its bin is the number of smaller ids there
-        BinAtom* out = b.bpos + size_t(slot) * N;
-        for (int i = t; i < N; i += 1024) {
-            const int bin = info[i];
-            int pos = start[bin];
-            for (int q = start[bin]; q < start[bin + 1]; ++q) pos += int(ids[q]) < i ? 1 : 0;
-            out[pos] = bin_record(g, load4(R, i), i, info[2 * N + i]);
+        if (rebuild) {  // uniform
+            // a copy held in scalar registers (in k_skin_image it would cost the idle steps)
+            const ImageGeom g = *(const ImageGeom*)cp(b.geom + slot);
+            bins_of_image(b, g, slot, start, ids, wsum);
         }
         __syncthreads();
     }
@@ -935,14 +1018,16 @@ void launch_skin_hold(const Launch& L, int hold, hipStream_t s)
 void launch_skin(const Launch& L, int all_images, hipStream_t s)
 {
     if (L.variants & (1u << VARIANT_SKIN_IMAGE)) k_skin_image<<<L.g[KIND_SIMAGE], 1024, 0, s>>>(L.bd, all_images);
-    if (!(L.variants & (1u << VARIANT_SKIN_LARGE))) return;
+    if (!(L.variants & (1u << VARIANT_BIN_IMAGE | 1u << VARIANT_BIN_TILES))) return;
     k_skin_check<<<L.g[KIND_ATOM4], CFNEB_TILE, 0, s>>>(L.bd, all_images);
+    if (L.variants & (1u << VARIANT_BIN_IMAGE)) k_skin_bins<<<L.g[KIND_BIMAGE], 1024, 0, s>>>(L.bd, all_images);
+    if (!(L.variants & (1u << VARIANT_BIN_TILES))) return;
     k_skin_decide<<<L.g[KIND_BAND], 16 * CFNEB_MAX_IMAGES, 0, s>>>(L.bd, all_images);
 }
 
 void launch_bins(const Launch& L, int all_images, hipStream_t s)
 {
-    if (!(L.variants & (1u << VARIANT_SKIN_LARGE))) return;
+    if (!(L.variants & (1u << VARIANT_BIN_TILES))) return;
     k_bin_assign<<<L.g[KIND_LATOM], CFNEB_TILE, 0, s>>>(L.bd, all_images);
     k_bin_scan<<<L.g[KIND_LIMAGE], 1024, 0, s>>>(L.bd, all_images);
     k_bin_scatter<<<L.g[KIND_LATOM], CFNEB_TILE, 0, s>>>(L.bd, all_images);
