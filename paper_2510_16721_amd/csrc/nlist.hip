@@ -42,11 +42,6 @@ __device__ inline size_t bin_base(const BandDev& b, int slot) { return size_t(sl
 
 // A lattice image (three counts) in 10-bit fields, as bin_assign stores it.
 __device__ inline int img_n(int v, int k) { return ((v >> (10 * k)) & 0x3FF) - 512; }
-// Sum of two triples of 4-bit counts (bits 20..31), each modulo 16.
-__device__ inline uint32_t add_images(uint32_t a, uint32_t b)
-{
-    return ((a & 0x77700000u) + (b & 0x77700000u)) ^ ((a ^ b) & 0x88800000u);
-}
 __device__ inline uint32_t pack_images(int n0, int n1, int n2)
 {
     return (uint32_t(n0 & 15) << 20) | (uint32_t(n1 & 15) << 24) | (uint32_t(n2 & 15) << 28);
@@ -270,7 +265,8 @@ __device__ inline bool image_is_far(const int (&img)[3])
 {
     return abs(img[0]) > 3 || abs(img[1]) > 3 || abs(img[2]) > 3;
 }
-// Atom i's record in bin order.
+// Atom i's record in bin order; its code carries the atom and 3 - im in each field, im its
+// lattice image (within 3 of the cell: others take cand_item, which does not read it).
 __device__ inline BinAtom bin_record(const ImageGeom& g, const double4& ri, int i, int im)
 {
     const double n0 = img_n(im, 0), n1 = img_n(im, 1), n2 = img_n(im, 2);
@@ -278,7 +274,7 @@ __device__ inline BinAtom bin_record(const ImageGeom& g, const double4& ri, int 
     a.x = float(ri.x - (n0 * g.h[0] + n1 * g.h[3] + n2 * g.h[6]));
     a.y = float(ri.y - (n0 * g.h[1] + n1 * g.h[4] + n2 * g.h[7]));
     a.z = float(ri.z - (n0 * g.h[2] + n1 * g.h[5] + n2 * g.h[8]));
-    a.code = uint32_t(i) | pack_images(-img_n(im, 0), -img_n(im, 1), -img_n(im, 2));
+    a.code = uint32_t(i) | pack_images(3 - img_n(im, 0), 3 - img_n(im, 1), 3 - img_n(im, 2));
     return a;
 }
 
@@ -666,13 +662,20 @@ __device__ void cand_item(const BandDev& b, BandState* st, int slot, int i)
 // of the group's atoms in turn, 64 records are tested at a time, one per lane, and the
 // lanes inside append their entries (ballot prefix).  A thread per atom instead walks its
 // stencil as a serial chain of loads with every test and append diverging inside the wave.
-// Bound by VALU issue (about 220 instructions an atom).  Building the lists of 22 images
-// of 97,555 LJ atoms: 3,180 us with a thread per atom, 850 us here.
+// Bound by vector issue (69 % of the slots) and the scattered stores of the entries.
+// Building the lists of 22 images of 97,555 LJ atoms: 3,180 us with a thread per atom, 850 us
+// in groups, 720 us with lane sets held as scalar masks (a compare a test instead of three
+// instructions), the record loop not unrolled (ten copies of it overran the instruction
+// cache) and images added as fields that cannot carry.
 //
-// Distances are FP32 between wrapped positions: each component is within 6 2^-24 of the
-// largest coordinate L (rounding of both positions, of the shift and of two sums), so
+// Distances are FP32 between wrapped positions: each component is within 10 2^-24 of the
+// largest coordinate L (1 for the rounding of either position, 2 for the shift from the
+// box's middle, at most 5 for sums no larger than the stencil; L is at least rcl here), so
 // FP32 r^2 decides outside a band around rcl^2 and the exact FP64 test inside it: the
 // list holds exactly the pairs that the FP64 test gives.
+// (97,555 LJ atoms | request of 16,383 | 2,743 carbon atoms: runs of 2 bins 17 | 24 | 13 % slower,
+// of 3 5 % faster | 7 % | 12 % slower; stages of 384 records 9 | 7 | 0 % slower; one atom to a
+// record read 5 % slower, three or four 5 to 8 %.)
 #define CAND_RUN 4
 #define CAND_STAGE 512
 #define CAND_SEGS 64
@@ -693,6 +696,27 @@ __device__ inline float lane_f(float v, int t)
 __device__ inline int lanes_below(unsigned long long mask)
 {
     return __builtin_amdgcn_mbcnt_hi(unsigned(mask >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(mask), 0u));
+}
+// The lanes of the (whole) wave where a condition holds, and the condition of a lane set:
+// scalar registers both ways.
+__device__ inline unsigned long long lanes_where(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ inline bool in_lanes(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// Minimum over the whole wave, in every lane.
+__device__ inline float wave_fmin(float v)
+{
+    v = fminf(v, __int_as_float(dpp_i32<0xB1>(__float_as_int(v))));
+    v = fminf(v, __int_as_float(dpp_i32<0x4E>(__float_as_int(v))));
+    v = fminf(v, __int_as_float(dpp_i32<0x141>(__float_as_int(v))));
+    v = fminf(v, __int_as_float(dpp_i32<0x140>(__float_as_int(v))));
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fminf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fminf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+// A record by its byte offset from a uniform base (fewer than 2^20 records).
+__device__ inline const gmem<const float4>* at_byte(const gmem<const float4>* p, uint32_t off)
+{
+    return reinterpret_cast<const gmem<const float4>*>(reinterpret_cast<const gmem<const char>*>(p) + off);
 }
 // LDS written by some lanes of a wave and read by others of the same wave.
 __device__ inline void wave_lds_fence()
@@ -726,7 +750,7 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
     for (int c = 0; c < 3; ++c)
         big = fmaxf(big, float(fabs(g->h[c]) + fabs(g->h[3 + c]) + fabs(g->h[6 + c])) * 1.000001f);
     const float rcl = float(b.rcl), rcl2 = float(b.rcl2), u = 0x1p-24f;
-    const float e = 1.7320509f * 6.f * u * big;
+    const float e = 1.7320509f * 10.f * u * big;
     const float delta = 1.01f * (2.f * rcl * e + e * e) + 12.f * u * rcl2;
     const float lo2 = uni(rcl2 - delta), hi2 = uni(rcl2 + delta);
     const int width = 2 * r + 1, zlo = z0 - r, zhi = z1 - 1 + r;
@@ -738,8 +762,9 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
         const float4 me = load4(bp, a0 + min(lane, na - 1));
         const uint32_t mec = __float_as_uint(me.w);
         const int id = nbr_j(mec);
-        // an entry's images are m + im_i - im_j: i's part, plus the 8 of the packing
-        const uint32_t mine = add_images(pack_images(8, 8, 8), add_images(~mec & 0xFFF00000u, pack_images(1, 1, 1)));
+        // an entry's fields are m + im_i - im_j + 8, in [1, 15]: sums of fields that never
+        // carry, im_i + 3 here, m + 2 of the stencil's cell, 3 - im_j of the record
+        const uint32_t mine = 0x66600000u - (mec & 0xFFF00000u);
         int cnt = 0;  // of lane's atom
         // atoms of one lattice image at a time (nearly always all of them), so the staged
         // records carry finished entries
@@ -751,81 +776,82 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
             todo &= ~members;
             float bx0 = part ? me.x : 1e30f, bx1 = part ? me.x : -1e30f, by0 = part ? me.y : 1e30f;
             float by1 = part ? me.y : -1e30f, bz0 = part ? me.z : 1e30f, bz1 = part ? me.z : -1e30f;
-            for (int off = 32; off > 0; off >>= 1) {
-                bx0 = fminf(bx0, __shfl_xor(bx0, off, 64));
-                bx1 = fmaxf(bx1, __shfl_xor(bx1, off, 64));
-                by0 = fminf(by0, __shfl_xor(by0, off, 64));
-                by1 = fmaxf(by1, __shfl_xor(by1, off, 64));
-                bz0 = fminf(bz0, __shfl_xor(bz0, off, 64));
-                bz1 = fmaxf(bz1, __shfl_xor(bz1, off, 64));
-            }
-            int n = 0;    // staged records
+            bx0 = wave_fmin(bx0), by0 = wave_fmin(by0), bz0 = wave_fmin(bz0);
+            bx1 = -wave_fmin(-bx1), by1 = -wave_fmin(-by1), bz1 = -wave_fmin(-bz1);
+            // positions from here on are relative to the box's middle
+            const float mx = 0.5f * (bx0 + bx1), my = 0.5f * (by0 + by1), mz = 0.5f * (bz0 + bz1);
+            const float px = me.x - mx, py = me.y - my, pz = me.z - mz;
+            const float wx = fmaxf(bx1 - mx, mx - bx0), wy = fmaxf(by1 - my, my - by0), wz = fmaxf(bz1 - mz, mz - bz0);
+            int n = 0;  // staged records
             // every member against the staged records, two atoms to a record read
             auto test = [&]() {
                 const int full = uni((n + 63) & ~63);
                 if (n + lane < full) lds.rec[n + lane].x = 3e18f;  // outside of any cutoff
                 wave_lds_fence();
+                constexpr int V = 2;
                 for (unsigned long long left = members; left;) {
-                    float xi[2], yi[2], zi[2], hi[2];
-                    uint32_t self[2];
-                    int t[2], i[2], k[2];
-                    uint32_t* out[2];
+                    float xi[V], yi[V], zi[V], hi[V];
+                    uint32_t self[V];
+                    int t[V], i[V], k[V];
+                    uint32_t* out[V];
 #pragma unroll
-                    for (int v = 0; v < 2; ++v) {
+                    for (int v = 0; v < V; ++v) {
                         hi[v] = left ? hi2 : -1.f;  // an odd last atom has no partner
                         t[v] = left ? __ffsll(left) - 1 : t[0];
                         left &= left - 1;
-                        xi[v] = lane_f(me.x, t[v]);
-                        yi[v] = lane_f(me.y, t[v]);
-                        zi[v] = lane_f(me.z, t[v]);
+                        xi[v] = lane_f(px, t[v]);
+                        yi[v] = lane_f(py, t[v]);
+                        zi[v] = lane_f(pz, t[v]);
                         i[v] = __builtin_amdgcn_readlane(id, t[v]);
                         k[v] = __builtin_amdgcn_readlane(cnt, t[v]);
                         self[v] = uint32_t(i[v]) | 0x88800000u;
                         out[v] = uni(Cs(b, slot) + cand_at(ccap, i[v], 0));
                     }
                     float4 next = *reinterpret_cast<const float4*>(&lds.rec[lane]);
+#pragma unroll 1
                     for (int c = 0; c < full; c += 64) {
                         const float4 rec = next;
                         next = *reinterpret_cast<const float4*>(&lds.rec[min(c + 64, CAND_STAGE - 64) + lane]);
                         const uint32_t ent = __float_as_uint(rec.w);
-                        float r2[2];
-                        bool in[2];
+                        // lane sets as scalar masks: the tests cost a compare each
+                        float r2[V];
+                        unsigned long long in[V], near[V], some = 0;
 #pragma unroll
-                        for (int v = 0; v < 2; ++v) {
+                        for (int v = 0; v < V; ++v) {
                             const float dx = rec.x - xi[v], dy = rec.y - yi[v], dz = rec.z - zi[v];
                             r2[v] = dx * dx + dy * dy + dz * dz;
-                            in[v] = int(r2[v] < hi[v]) & int(ent != self[v]);
+                            in[v] = lanes_where(r2[v] < hi[v]) & lanes_where(ent != self[v]);
+                            near[v] = in[v] & lanes_where(r2[v] >= lo2);
+                            some |= near[v];
                         }
-                        // rare: FP32 cannot tell
-                        if (__any((int(in[0]) & int(r2[0] >= lo2)) | (int(in[1]) & int(r2[1] >= lo2)))) {
-                            for (int v = 0; v < 2; ++v) {
-                                if (!(in[v] && r2[v] >= lo2)) continue;
-                                const double4 p = load4(R, i[v]), o = load4(R, nbr_j(ent));
-                                const double ri[3] = {p.x, p.y, p.z};
-                                double h[9], d[3];
-                                for (int w = 0; w < 9; ++w) h[w] = g->h[w];
-                                const double rr = exact_r2(ri, o.x, o.y, o.z, h, nbr_n(ent, 0), nbr_n(ent, 1),
-                                                           nbr_n(ent, 2), d);
-                                in[v] = rr < b.rcl2;
+                        if (some) {  // rare: FP32 cannot tell
+                            for (int v = 0; v < V; ++v) {
+                                bool out_of = false;
+                                if (in_lanes(near[v])) {
+                                    const double4 p = load4(R, i[v]), o = load4(R, nbr_j(ent));
+                                    const double ri[3] = {p.x, p.y, p.z};
+                                    double h[9], d[3];
+                                    for (int w = 0; w < 9; ++w) h[w] = g->h[w];
+                                    const double rr = exact_r2(ri, o.x, o.y, o.z, h, nbr_n(ent, 0), nbr_n(ent, 1),
+                                                               nbr_n(ent, 2), d);
+                                    out_of = !(rr < b.rcl2);
+                                }
+                                in[v] &= ~lanes_where(out_of);
                             }
                         }
 #pragma unroll
-                        for (int v = 0; v < 2; ++v) {
-                            const unsigned long long mask = __ballot(in[v]);
-                            const int pos = k[v] + lanes_below(mask);
-                            k[v] += int(__popcll(mask));
+                        for (int v = 0; v < V; ++v) {
+                            const int pos = k[v] + lanes_below(in[v]);
+                            k[v] += int(__popcll(in[v]));
+                            if (k[v] > ccap) in[v] &= lanes_where(pos < ccap);  // uniform
                             // entry pos at word (pos / 4) 256 + pos % 4 of the atom's column
-                            const uint32_t off = ((uint32_t(pos) << 8) & ~1023u) | ((uint32_t(pos) & 3u) << 2);
+                            const uint32_t off = (uint32_t(pos) << 8) - __umul24(uint32_t(pos) & 3u, 252u);
                             gmem<char>* at = gp(reinterpret_cast<char*>(out[v])) + off;
-                            if (k[v] <= ccap) {  // uniform
-                                if (in[v]) *reinterpret_cast<gmem<uint32_t>*>(at) = ent;
-                            } else {
-                                if (in[v] && pos < ccap) *reinterpret_cast<gmem<uint32_t>*>(at) = ent;
-                            }
+                            if (in_lanes(in[v])) *reinterpret_cast<gmem<uint32_t>*>(at) = ent;
                         }
                     }
-                    cnt = lane == t[0] ? k[0] : cnt;
-                    if (hi[1] > 0.f) cnt = lane == t[1] ? k[1] : cnt;
+#pragma unroll
+                    for (int v = V - 1; v >= 0; --v) cnt = lane == t[v] ? k[v] : cnt;
                 }
                 wave_lds_fence();
                 n = 0;
@@ -844,10 +870,10 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
                     CandSeg sg;
                     sg.lo = start[base + zs];
                     sg.count = min(start[base + ze], N) - sg.lo;
-                    sg.images = add_images(pack_images(m0, m1, m2), image);
-                    sg.x = float(double(m0) * g->h[0] + double(m1) * g->h[3] + double(m2) * g->h[6]);
-                    sg.y = float(double(m0) * g->h[1] + double(m1) * g->h[4] + double(m2) * g->h[7]);
-                    sg.z = float(double(m0) * g->h[2] + double(m1) * g->h[5] + double(m2) * g->h[8]);
+                    sg.images = pack_images(m0 + 2, m1 + 2, m2 + 2) + image;
+                    sg.x = float(double(m0) * g->h[0] + double(m1) * g->h[3] + double(m2) * g->h[6] - double(mx));
+                    sg.y = float(double(m0) * g->h[1] + double(m1) * g->h[4] + double(m2) * g->h[7] - double(my));
+                    sg.z = float(double(m0) * g->h[2] + double(m1) * g->h[5] + double(m2) * g->h[8] - double(mz));
                     lds.seg[lane] = sg;
                 }
                 wave_lds_fence();
@@ -866,7 +892,7 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
                             sg[w] = lds.seg[min(sw, ns - 1)];
                             if (sw >= ns) sg[w].count = 0;
                             more |= int(k0 + 32 < sg[w].count);
-                            a[w] = load4(bp, k < sg[w].count ? sg[w].lo + k : first);
+                            a[w] = load4(at_byte(bp, uint32_t(k < sg[w].count ? sg[w].lo + k : first) * 16u), 0);
                         }
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -875,14 +901,13 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
                             a[w].x += sg[w].x;
                             a[w].y += sg[w].y;
                             a[w].z += sg[w].z;
-                            const float ex = fmaxf(fmaxf(bx0 - a[w].x, a[w].x - bx1), 0.f);
-                            const float ey = fmaxf(fmaxf(by0 - a[w].y, a[w].y - by1), 0.f);
-                            const float ez = fmaxf(fmaxf(bz0 - a[w].z, a[w].z - bz1), 0.f);
+                            const float ex = fmaxf(fabsf(a[w].x) - wx, 0.f);
+                            const float ey = fmaxf(fabsf(a[w].y) - wy, 0.f);
+                            const float ez = fmaxf(fabsf(a[w].z) - wz, 0.f);
                             const bool keep = int(k < sg[w].count) & int(ex * ex + ey * ey + ez * ez < hi2);
                             const unsigned long long mask = __ballot(keep);
                             if (keep) {
-                                const uint32_t code = __float_as_uint(a[w].w);
-                                a[w].w = __uint_as_float((code & 0xFFFFFu) | add_images(code, sg[w].images));
+                                a[w].w = __uint_as_float(__float_as_uint(a[w].w) + sg[w].images);
                                 *reinterpret_cast<float4*>(&lds.rec[n + lanes_below(mask)]) = a[w];
                             }
                             n = uni(n + int(__popcll(mask)));
