@@ -235,10 +235,19 @@ __global__ void __launch_bounds__(CFNEB_MAX_BANDS) k_geom(BatchDev bd, int all_i
 // ---------------------------------------------------------------- construction
 // staging: RA (3N, row-major) | RB (3N) | hA (9) | hB (9) | BB (9) | h0inv (9) | hBinv (9)
 //          | D_B (9)
-__global__ void k_init_endpoints(BandDev b)
+// Also the band's own table of one.  Cells and table entry come as kernel arguments: a copy
+// of a few bytes from pageable memory holds the host for 8 to 40 us (four of them made a
+// tenth of a creation).
+__global__ void k_init_endpoints(BandDev b, EndCells cells, BandDev* table, int* live)
 {
+    *table = b;
+    *live = 1;
     double* sg = b.staging + 6 * size_t(b.N);
-    const double* hB = sg + 9;
+    const double* hB = cells.b;
+    for (int q = 0; q < 9; ++q) {
+        sg[q] = cells.a[q];
+        sg[9 + q] = cells.b[q];
+    }
     double* BB = sg + 18;
     double* h0inv = sg + 27;
     double* hBinv = sg + 36;
@@ -353,7 +362,10 @@ __global__ void k_image_positions(BandDev b, int k)
     for (int c = 0; c < 3; ++c) b.staging[3 * size_t(i) + c] = x * D[c] + y * D[3 + c] + z * D[6 + c];
 }
 
-void launch_init_endpoints(const BandDev& b, hipStream_t s) { k_init_endpoints<<<1, 1, 0, s>>>(b); }
+void launch_init_endpoints(const BandDev& b, const Launch& L, const EndCells& cells, hipStream_t s)
+{
+    k_init_endpoints<<<1, 1, 0, s>>>(b, cells, const_cast<BandDev*>(L.bd.bands), const_cast<int*>(L.bd.live));
+}
 
 void launch_init_images(const BandDev& b, int M, hipStream_t s)
 {

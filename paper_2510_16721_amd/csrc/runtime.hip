@@ -464,13 +464,17 @@ int tune_force_grid(Launch& L, hipStream_t s)
     return rc;
 }
 
+// The graph with the refinement phase is made only for bands that can refine (50 of the
+// 115 us that both take).
 int capture_band_graphs(cfneb_band* b)
 {
     if (tune_force_grid(b->launch, b->stream) != CFNEB_OK) return fail(b, CFNEB_EHIP, "tuning");
-    HIP_TRY(b, hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeRelaxed));
-    launch_step(b->launch, b->capture_stream);
-    HIP_TRY(b, hipStreamEndCapture(b->capture_stream, &b->graph));
-    HIP_TRY(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
+    if (b->p.refine_every > 0) {
+        HIP_TRY(b, hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeRelaxed));
+        launch_step(b->launch, b->capture_stream);
+        HIP_TRY(b, hipStreamEndCapture(b->capture_stream, &b->graph));
+        HIP_TRY(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
+    }
     HIP_TRY(b, hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeRelaxed));
     launch_step_core(b->launch, b->capture_stream);
     HIP_TRY(b, hipStreamEndCapture(b->capture_stream, &b->graph_core));
@@ -488,10 +492,10 @@ void drop_band_graphs(cfneb_band* b)
     b->graph = b->graph_core = nullptr;
 }
 
-// Both step graphs, or neither (a failed capture leaves none behind).
+// Every step graph that the band needs, or none (a failed capture leaves none behind).
 int ensure_graph(cfneb_band* b)
 {
-    if ((b->exec && b->exec_core) || !b->use_graph) return CFNEB_OK;
+    if (b->exec_core || !b->use_graph) return CFNEB_OK;
     drop_band_graphs(b);
     const int rc = capture_band_graphs(b);
     if (rc != CFNEB_OK) drop_band_graphs(b);
@@ -578,18 +582,14 @@ int init_band(cfneb_band* b, const double* pos_init, const double* cell_init, co
         launch_fill_zero(workspace, b->L.total, b->stream);
     else
         HIP_TRY(b, hipMemsetAsync(workspace, 0, b->L.total, b->stream));
-    // upload the endpoints to the staging area: RA | RB | hA | hB
+    // the endpoints' positions to the staging area: RA | RB
     double* stg = b->d.staging;
     HIP_TRY(b, hipMemcpyAsync(stg, pos_init, 3 * N * sizeof(double), hipMemcpyHostToDevice, b->stream));
     HIP_TRY(b, hipMemcpyAsync(stg + 3 * N, pos_final, 3 * N * sizeof(double), hipMemcpyHostToDevice, b->stream));
-    HIP_TRY(b, hipMemcpyAsync(stg + 6 * N, cell_init, 9 * sizeof(double), hipMemcpyHostToDevice, b->stream));
-    HIP_TRY(b, hipMemcpyAsync(stg + 6 * N + 9, cell_final, 9 * sizeof(double), hipMemcpyHostToDevice, b->stream));
-    static const int one = 1;
-    HIP_TRY(b, hipMemcpyAsync(const_cast<BandDev*>(b->launch.bd.bands), &b->d, sizeof(BandDev),
-                              hipMemcpyHostToDevice, b->stream));
-    HIP_TRY(b, hipMemcpyAsync(const_cast<int*>(b->launch.bd.live), &one, sizeof(int), hipMemcpyHostToDevice,
-                              b->stream));
-    launch_init_endpoints(b->d, b->stream);
+    EndCells cells;
+    std::copy(cell_init, cell_init + 9, cells.a);
+    std::copy(cell_final, cell_final + 9, cells.b);
+    launch_init_endpoints(b->d, b->launch, cells, b->stream);
     launch_init_images(b->d, b->p.n_images, b->stream);
     launch_init_state(b->d, b->p.n_images, b->stream);
     launch_evaluate(b->launch, 1, b->stream);
@@ -761,7 +761,7 @@ int cfneb_step(cfneb_band* b, int max_steps, double f_tol, int* steps_done, doub
     const int check_every = 16;
     for (int s = 0; s < max_steps; ++s, ++next) {
         const bool with_refine = refine_due(b->p, next);
-        if (b->exec) {
+        if (b->exec_core) {
             HIP_TRY(b, hipGraphLaunch(with_refine ? b->exec : b->exec_core, b->stream));
         } else {
             rc = launch_step_direct(b, with_refine);
