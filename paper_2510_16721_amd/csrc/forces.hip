@@ -156,6 +156,18 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
     store_ev_partials(b, slot, tile, v);
 }
 
+// Loads at a 32-bit byte offset from a uniform base (one address add per load).
+__device__ inline uint4 ld_u128(const void* base, uint32_t off)
+{
+    return load4(reinterpret_cast<const gmem<const uint4>*>(gp(static_cast<const char*>(base)) + off), 0);
+}
+__device__ inline uint4 ld_u96(const void* base, uint32_t off)
+{
+    const gmem<const uint32_t>* p =
+        reinterpret_cast<const gmem<const uint32_t>*>(gp(static_cast<const char*>(base)) + off);
+    return make_uint4(p[0], p[1], p[2], 0u);
+}
+
 // FP32 bands whose cell is wide enough (ImageGeom::wrap): the separation comes from
 // the fixed-point fractional coordinates, one 12-byte gather per candidate and no
 // lattice-shift arithmetic: the wrapped 32-bit difference of two coordinates is the
@@ -169,17 +181,6 @@ __device__ void lj_cand_item(const BandDev& b, BandState* st, int slot, int tile
 // cache's cycles (a lane's line each).  The next four entries load during this batch, and a
 // pair outside rc is dropped by one select: 341 -> 338 us there; in a batch of 64 bands of
 // up to 32,000 atoms 224 -> 206 us a step here and 202 -> 180 us with several lanes.
-// Loads at a 32-bit byte offset from a uniform base (one address add per load).
-__device__ inline uint4 ld_u128(const void* base, uint32_t off)
-{
-    return load4(reinterpret_cast<const gmem<const uint4>*>(gp(static_cast<const char*>(base)) + off), 0);
-}
-__device__ inline uint4 ld_u96(const void* base, uint32_t off)
-{
-    const gmem<const uint32_t>* p = reinterpret_cast<const gmem<const uint32_t>*>(gp(static_cast<const char*>(base)) + off);
-    return make_uint4(p[0], p[1], p[2], 0u);
-}
-
 template <int K>
 __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int tile)
 {

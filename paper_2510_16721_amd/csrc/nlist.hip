@@ -42,6 +42,7 @@ __device__ inline size_t bin_base(const BandDev& b, int slot) { return size_t(sl
 
 // A lattice image (three counts) in 10-bit fields, as bin_assign stores it.
 __device__ inline int img_n(int v, int k) { return ((v >> (10 * k)) & 0x3FF) - 512; }
+// Three counts modulo 16 in the fields of a list entry.
 __device__ inline uint32_t pack_images(int n0, int n1, int n2)
 {
     return (uint32_t(n0 & 15) << 20) | (uint32_t(n1 & 15) << 24) | (uint32_t(n2 & 15) << 28);
@@ -656,7 +657,7 @@ __device__ void cand_item(const BandDev& b, BandState* st, int slot, int i)
     if (cnt > ccap) set_error(st, CFNEB_ENEIGH);
 }
 
-// Every other image: one wave per group of CAND_RUN bins of a row along the third axis.
+// Every other image: one wave per group of up to CAND_RUN bins of a row along the third axis.
 // The wave stages the records of the group's stencil in LDS once, shifted into the
 // group's frame and cut to those within rcl of the group's bounding box; then, for each
 // of the group's atoms in turn, 64 records are tested at a time, one per lane, and the
@@ -673,10 +674,16 @@ __device__ void cand_item(const BandDev& b, BandState* st, int slot, int i)
 // box's middle, at most 5 for sums no larger than the stencil; L is at least rcl here), so
 // FP32 r^2 decides outside a band around rcl^2 and the exact FP64 test inside it: the
 // list holds exactly the pairs that the FP64 test gives.
-// (97,555 LJ atoms | request of 16,383 | 2,743 carbon atoms: runs of 2 bins 17 | 24 | 13 % slower,
-// of 3 5 % faster | 7 % | 12 % slower; stages of 384 records 9 | 7 | 0 % slower; one atom to a
-// record read 5 % slower, three or four 5 to 8 %.)
+// (97,555 LJ atoms | request of 16,383: runs of 2 bins 17 | 24 % slower, of 3 5 % faster | 7 %
+// slower; stages of 384 records 9 | 7 % slower; one atom to a record read 5 % slower, three or
+// four 5 to 8 %.)  Full-width bins hold a quarter of the atoms (two or three), so their runs
+// are longer: 73,728 carbon atoms of graphite x 12 images 390 us a build in runs of 4, 325 of
+// 12; 39,303 of diamond x 7 images 64 | 62 us mean a step; below 16,384 atoms the groups are
+// too few for that (2,743 x 11 images 15.3 us in runs of 8, 18.1 of 12).  A row's bins are
+// shared evenly among its groups.
 #define CAND_RUN 4
+#define CAND_RUN_SPARSE 12
+#define CAND_RUN_SMALL 8
 #define CAND_STAGE 512
 #define CAND_SEGS 64
 struct CandSeg {
@@ -738,7 +745,7 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
 {
     const int lane = int(threadIdx.x) & 63;
     const int nb0 = g->nb[0], nb1 = g->nb[1], nb2 = g->nb[2], r = g->sub, N = b.N, ccap = b.ccap;
-    const int row = q / gz, z0 = (q - row * gz) * CAND_RUN, z1 = min(z0 + CAND_RUN, nb2);
+    const int row = q / gz, zg = q - row * gz, z0 = zg * nb2 / gz, z1 = (zg + 1) * nb2 / gz;
     const int b0 = row / nb1, b1 = row - b0 * nb1;
     const gmem<const int>* __restrict__ start = gp<const int>(b.bstart + bin_base(b, slot));
     const int first = uni(start[row * nb2 + z0]), last = uni(min(start[row * nb2 + z1], N));
@@ -877,9 +884,10 @@ __device__ void cand_group(const BandDev& b, BandState* st, const cmem<ImageGeom
                     lds.seg[lane] = sg;
                 }
                 wave_lds_fence();
-                // 32 lanes to a segment; the loads of eight segments are in flight together
-                // (a longer segment, of a clustered structure, takes further rounds)
-                constexpr int U = 4;
+                // 32 lanes to a segment; the loads of ten segments are in flight together, so
+                // a 3 x 3 stencil takes one round and a 5 x 5 three (a longer segment, of a
+                // clustered structure, takes further rounds): 412 us with eight, 399 with ten
+                constexpr int U = 5;
                 for (int p = 0; p < ns; p += 2 * U) {
                     for (int k0 = 0;; k0 += 32) {
                         float4 a[U];
@@ -952,7 +960,8 @@ k_cand(BatchDev bd, int all_images)
             continue;
         }
         // the tiles of an image share its groups evenly, in runs
-        const int gz = (g->nb[2] + CAND_RUN - 1) / CAND_RUN, total = g->nb[0] * g->nb[1] * gz;
+        const int run = g->sub > 1 ? CAND_RUN : b.N > 16384 ? CAND_RUN_SPARSE : CAND_RUN_SMALL;
+        const int gz = (g->nb[2] + run - 1) / run, total = g->nb[0] * g->nb[1] * gz;
         const int tiles = kind_tiles(b, KIND_CAND), per = (total + tiles - 1) / tiles;
         const int end = min((it.tile + 1) * per, total), wave = uni(int(threadIdx.x) >> 6);
         // (the waves take turns at the first group, so an uneven share goes round)

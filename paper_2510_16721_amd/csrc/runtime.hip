@@ -132,7 +132,8 @@ void size_grids(Launch& L, long long atom_tiles, long long row_tiles, long long 
     L.g[KIND_ROW] = grid_for(row_tiles, CFNEB_GRID_TILES);
     L.g[KIND_BIN] = grid_for(bin_tiles, CFNEB_GRID_TILES);
     L.g[KIND_CAND] = grid_for(2 * atom_tiles, CFNEB_GRID_TILES);  // tiles of 128 atoms
-    L.g[KIND_IMAGE] = L.g[KIND_LIMAGE] = L.g[KIND_BIMAGE] = L.g[KIND_SIMAGE] = L.g[KIND_DIMAGE] = grid_for(images, CFNEB_GRID_IMAGES);
+    L.g[KIND_IMAGE] = L.g[KIND_DIMAGE] = grid_for(images, CFNEB_GRID_IMAGES);
+    L.g[KIND_LIMAGE] = L.g[KIND_BIMAGE] = L.g[KIND_SIMAGE] = L.g[KIND_IMAGE];
     L.g[KIND_LATOM] = L.g[KIND_ATOM];
     L.g[KIND_IVAL] = grid_for(row_tiles, CFNEB_GRID_TILES);
     L.g[KIND_SLOTROW] = grid_for(row_tiles, CFNEB_GRID_TILES);
