@@ -521,6 +521,15 @@ __device__ void ts_many_bonds(const BandDev& b, int slot, int tile)
     store_ev_partials<true>(b, slot, tile, acc);
 }
 
+// A band's table entry read again: what a rare branch or a later part alone uses stays out
+// of the scalar registers until then (98,304 atoms x 22 images: 279 -> 98 reloads of spilled
+// scalars in the code of the bond kernel, 122 -> 112 us).
+__device__ inline BandDev band_again(const cmem<BandDev>* p)
+{
+    asm volatile("" : "+s"(p));  // (a new address to the compiler)
+    return *(const BandDev*)p;
+}
+
 // Neighbours of atom i by the exact test of its candidates (as the candidate filter
 // does for LJ), then u_i, P_ij and the per-atom virial from the bond vectors; wave
 // partials of (E, V) in FP64.  The first four bonds go to this thread's LDS slots
@@ -528,7 +537,8 @@ __device__ void ts_many_bonds(const BandDev& b, int slot, int tile)
 // and then to registers; an atom with more bonds writes them to global scratch and
 // takes the general path.
 template <typename T>
-__device__ bool ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, int tile, vec4_t<T>* lbond, int* lcid)
+__device__ bool ts_filter_bonds_item(const cmem<BandDev>* src, const BandDev& b, BandState* st, int slot, int tile,
+                                     vec4_t<T>* lbond, int* lcid)
 {
     constexpr int MB = TS_LDS_BONDS;
     const int tid = threadIdx.x;
@@ -541,8 +551,6 @@ __device__ bool ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
         const gmem<const R3>* __restrict__ R = gp<const R3>(Rs(b, slot));
         const gmem<const uint4>* __restrict__ cand = gp<const uint4>(reinterpret_cast<const uint4*>(Cs(b, slot)));
         gmem<P3<T>>* __restrict__ Pout = gp(reinterpret_cast<P3<T>*>(b.P) + size_t(slot) * b.ccap * N);
-        vec4_t<T>* dv = reinterpret_cast<vec4_t<T>*>(b.dvec) + size_t(slot) * b.cap * N;
-        int* bcid = reinterpret_cast<int*>(b.bcid) + size_t(slot) * b.cap * N;
         double h[9];
         for (int q = 0; q < 9; ++q) h[q] = g->h[q];
         const double4 r4 = load4(R, i);
@@ -550,7 +558,7 @@ __device__ bool ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
         const int nc = gp<const int>(b.ncand)[size_t(slot) * N + i];
         const double rc2 = b.rc2;
         const int cap = b.cap;
-        if (cp(b.skst + slot)->rebuild) ts_reverse_candidates(b, st, slot, i, nc);
+        if (cp(b.skst + slot)->rebuild) ts_reverse_candidates(band_again(src), st, slot, i, nc);
         const vec4_t<T> zero{};
         int cnt = 0;
         // four candidates at a time (carbon atoms have three or four): one round of
@@ -585,8 +593,10 @@ __device__ bool ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
                         lbond[cnt * CFNEB_TILE + tid] = v;
                         lcid[cnt * CFNEB_TILE + tid] = e0 + u;
                     } else {
-                        dv[size_t(cnt) * N + i] = v;
-                        bcid[size_t(cnt) * N + i] = e0 + u;
+                        const BandDev f = band_again(src);
+                        const size_t at = (size_t(slot) * f.cap + cnt) * f.N + i;
+                        reinterpret_cast<vec4_t<T>*>(f.dvec)[at] = v;
+                        reinterpret_cast<int*>(f.bcid)[at] = e0 + u;
                     }
                 }
                 ++cnt;
@@ -595,7 +605,7 @@ __device__ bool ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
         if (cnt > cap) set_error(st, CFNEB_ENEIGH);
         nb = min(cnt, cap);
         if (nb <= MB) {
-            const TersoffT<T> P(b);
+            const TersoffT<T> P(band_again(src));
             vec4_t<T> bond[MB];
 #pragma unroll
             for (int e = 0; e < MB; ++e) bond[e] = (e < nb) ? lbond[e * CFNEB_TILE + tid] : zero;
@@ -605,10 +615,12 @@ __device__ bool ts_filter_bonds_item(const BandDev& b, BandState* st, int slot, 
     const bool crowded = __any(nb > MB);  // uniform over the wave
     if (crowded && i < b.N) {
         // the wave's counts, and every bond of such atoms, for ts_many_bonds
-        gp(b.ncnt)[size_t(slot) * N + i] = nb;
+        const BandDev f = band_again(src);
+        const size_t N = f.N;
+        gp(f.ncnt)[size_t(slot) * N + i] = nb;
         if (nb > MB) {
-            vec4_t<T>* dv = reinterpret_cast<vec4_t<T>*>(b.dvec) + size_t(slot) * b.cap * N;
-            int* bcid = reinterpret_cast<int*>(b.bcid) + size_t(slot) * b.cap * N;
+            vec4_t<T>* dv = reinterpret_cast<vec4_t<T>*>(f.dvec) + size_t(slot) * f.cap * N;
+            int* bcid = reinterpret_cast<int*>(f.bcid) + size_t(slot) * f.cap * N;
             for (int e = 0; e < MB; ++e) {
                 dv[size_t(e) * N + i] = lbond[e * CFNEB_TILE + tid];
                 bcid[size_t(e) * N + i] = lcid[e * CFNEB_TILE + tid];
@@ -631,7 +643,7 @@ __device__ void ts_filter_bonds_loop(const BatchDev& bd, int all_images, int var
         const BandDev b = band_ro(bd, it.band);
         const cmem<BandState>* sr = cp(b.st);
         if (int(band_variant(b) != variant) | int(band_stopped(sr))) continue;  // uniform over the block
-        if (ts_filter_bonds_item<T>(b, b.st, sr->slot[it.image], it.tile, lbond, lcid)) crowded |= 1ull << n;
+        if (ts_filter_bonds_item<T>(cp(bd.bands) + it.band, b, b.st, sr->slot[it.image], it.tile, lbond, lcid)) crowded |= 1ull << n;
     }
     // the atoms with more bonds than the registers take, in a walk of their own: next to the
     // other bonds their code costs the common path a quarter in registers
