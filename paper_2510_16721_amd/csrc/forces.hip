@@ -311,9 +311,12 @@ __device__ __forceinline__ void lj_item(const BandDev& b, BandState* st, int slo
 }
 
 // Bands of one lane per atom (the large ones).  Four waves per SIMD without a spill: five
-// with one ran 346 us where four run 338 (97,555 atoms x 22 images, FP32).
+// with one ran 346 us where four run 338 (97,555 atoms x 22 images, FP32).  Asked for by
+// name: left alone the compiler also ends at four, on a schedule that runs 349 us to 341 on
+// the persistent grid and 334 to 332 with a block per tile.
 template <typename T>
-__global__ void __launch_bounds__(CFNEB_TILE) k_lj_one(BatchDev bd, int all_images, int variant)
+__global__ void __launch_bounds__(CFNEB_TILE) __attribute__((amdgpu_waves_per_eu(4)))
+k_lj_one(BatchDev bd, int all_images, int variant)
 {
     ItemLoopRO loop(bd, KIND_LJ1, all_images);
     Item it;
