@@ -288,7 +288,9 @@ __device__ void scalars_item(const BandDev& b, BandState* st)
         double cp = 0.0, cm = 0.0;
         if (nt > 0.0 && !b.relax) {
             const double ft = (a * d[3] + c * d[4]) / nt;
-            const double s = (k == ci) ? -2.0 * ft : b.k_spring * (sqrt(d[0]) - sqrt(d[1])) - ft;
+            // (images apart by a translation alone leave these squares to rounding, either sign)
+            const double s =
+                (k == ci) ? -2.0 * ft : b.k_spring * (sqrt(fmax(d[0], 0.0)) - sqrt(fmax(d[1], 0.0))) - ft;
             cp = s * a / nt;
             cm = s * c / nt;
         }
