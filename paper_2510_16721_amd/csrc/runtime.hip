@@ -419,10 +419,16 @@ int launch_step_direct(cfneb_band* b, bool with_refine)
 int tune_force_grid(Launch& L, hipStream_t s)
 {
     const unsigned cand[2] = {L.g[KIND_TS], L.g_force_tile};
-    // CFNEB_FORCE_GRID=persistent|tile fixes the choice (tests, reproducible timing)
+    // CFNEB_FORCE_GRID=persistent|tile|<blocks> fixes the choice (tests, reproducible timing)
     const char* fixed = std::getenv("CFNEB_FORCE_GRID");
     if (fixed && (std::strcmp(fixed, "persistent") == 0 || std::strcmp(fixed, "tile") == 0)) {
         L.g_force = cand[fixed[0] == 'p' ? 0 : 1];
+        return CFNEB_OK;
+    }
+    char* end = nullptr;
+    const long blocks = fixed ? std::strtol(fixed, &end, 10) : 0;
+    if (blocks > 0 && *end == '\0') {
+        L.g_force = grid_for(std::min(blocks, 1L << 30), L.g_force_tile);
         return CFNEB_OK;
     }
     if (cand[0] == cand[1]) {

@@ -535,10 +535,11 @@ __device__ inline BandDev band_again(const cmem<BandDev>* p)
 // partials of (E, V) in FP64.  The first four bonds go to this thread's LDS slots
 // (an LDS store at a per-lane index, where registers would need a select per slot)
 // and then to registers; an atom with more bonds writes them to global scratch and
-// takes the general path.
+// is left to ts_many_bonds.  Returns whether the wave has such atoms; its counts are
+// written if it has, and always where `counts` is set.
 template <typename T>
 __device__ bool ts_filter_bonds_item(const cmem<BandDev>* src, const BandDev& b, BandState* st, int slot, int tile,
-                                     vec4_t<T>* lbond, int* lcid)
+                                     bool counts, vec4_t<T>* lbond, int* lcid)
 {
     constexpr int MB = TS_LDS_BONDS;
     const int tid = threadIdx.x;
@@ -613,7 +614,7 @@ __device__ bool ts_filter_bonds_item(const cmem<BandDev>* src, const BandDev& b,
         }
     }
     const bool crowded = __any(nb > MB);  // uniform over the wave
-    if (crowded && i < b.N) {
+    if ((crowded || counts) && i < b.N) {
         // the wave's counts, and every bond of such atoms, for ts_many_bonds
         const BandDev f = band_again(src);
         const size_t N = f.N;
@@ -638,12 +639,15 @@ __device__ void ts_filter_bonds_loop(const BatchDev& bd, int all_images, int var
     __shared__ int lcid[TS_LDS_BONDS * CFNEB_TILE];
     ItemLoopRO loop(bd, KIND_TS, all_images);
     Item it;
-    unsigned long long crowded = 0;  // bit n (63: and later ones): this wave of item n
+    // bit n: this wave of item n; bit 63 also of every later one, so from there on each wave
+    // writes its counts, crowded or not: those of an earlier evaluation are not read again
+    unsigned long long crowded = 0;
     for (int n = 0; loop.next(it); n = min(n + 1, 63)) {
         const BandDev b = band_ro(bd, it.band);
         const cmem<BandState>* sr = cp(b.st);
         if (int(band_variant(b) != variant) | int(band_stopped(sr))) continue;  // uniform over the block
-        if (ts_filter_bonds_item<T>(cp(bd.bands) + it.band, b, b.st, sr->slot[it.image], it.tile, lbond, lcid)) crowded |= 1ull << n;
+        if (ts_filter_bonds_item<T>(cp(bd.bands) + it.band, b, b.st, sr->slot[it.image], it.tile, n == 63, lbond, lcid))
+            crowded |= 1ull << n;
     }
     // the atoms with more bonds than the registers take, in a walk of their own: next to the
     // other bonds their code costs the common path a quarter in registers
