@@ -594,65 +594,129 @@ __device__ inline void wrap_bin(int v, int nb, int& a, int& m)
     }
 }
 
-// Candidates of atom i, one thread: every (j, n) within rcl in stencil order; R_ref = R.
-// Serves images whose stencil spans more than one neighbouring cell (cells narrower than
-// rcl) or with atoms more than three cells away, where 4-bit lattice images could wrap.
-__device__ void cand_item(const BandDev& b, BandState* st, int slot, int i)
+// Candidates of the atom of record p (bin order), two neighbouring lanes: every (j, n) within
+// rcl in stencil order; R_ref = R.  Serves images whose stencil spans more than one neighbouring
+// cell (cells narrower than rcl) or with atoms more than three cells away, where 4-bit
+// lattice images could wrap.  Each lane takes four of eight records at a time.  FP32 between
+// wrapped positions decides outside a band around rcl^2 (a component: 1 2^-24 of the largest
+// coordinate L for the rounding of either position and for their difference, reach for that of
+// the shift, 1 + reach for the sum), the exact FP64 test inside it; lattice images come with
+// the records unless the image's atoms are far.
+// Bound by the chain of a lane's record loads: 3 images of 55,295 LJ atoms written five cells
+// away 255 us a build (570 us with one lane an atom and FP64 tests of gathered positions, one
+// at a time), a step that builds 7 images of 102,399 atoms in a cell one lattice constant
+// thick 1.05 ms (2.79 ms).
+__device__ void cand_item(const BandDev& b, BandState* st, int slot, int p, int half)
 {
-    const ImageGeom& g = b.geom[slot];
+    const cmem<ImageGeom>* g = cp(b.geom + slot);
     const gmem<const R3>* __restrict__ R = gp<const R3>(Rs(b, slot));
-    const double4 r4 = load4(R, i);
     const gmem<const int>* __restrict__ start = gp<const int>(b.bstart + bin_base(b, slot));
-    const BinAtom* __restrict__ bp = b.bpos + size_t(slot) * b.N;
-    const int* __restrict__ img = binfo_of(b, slot, 2);
+    const gmem<const float4>* __restrict__ bp =
+        gp<const float4>(reinterpret_cast<const float4*>(b.bpos + size_t(slot) * b.N));
+    const gmem<const int>* __restrict__ img = gp<const int>(binfo_of(b, slot, 2));
+    const float4 me = load4(bp, p);
+    const int i = nbr_j(__float_as_uint(me.w));
+    const double4 r4 = load4(R, i);
     gmem<uint32_t>* __restrict__ cand = gp(Cs(b, slot));
 
-    double h[9];
-    for (int q = 0; q < 9; ++q) h[q] = g.h[q];
     const double ri[3] = {r4.x, r4.y, r4.z};
-    gmem<float>* __restrict__ Rr = gp(b.Rref + size_t(slot) * slot_rows(b));
-    Rr[i] = float(ri[0]);
-    Rr[b.ld + i] = float(ri[1]);
-    Rr[2 * size_t(b.ld) + i] = float(ri[2]);
+    if (half == 0) {
+        gmem<float>* __restrict__ Rr = gp(b.Rref + size_t(slot) * slot_rows(b));
+        Rr[i] = float(ri[0]);
+        Rr[b.ld + i] = float(ri[1]);
+        Rr[2 * size_t(b.ld) + i] = float(ri[2]);
+    }
     const int bin = binfo_of(b, slot, 0)[i], im = img[i];
-    const int nb0 = g.nb[0], nb1 = g.nb[1], nb2 = g.nb[2];
+    const int nb0 = g->nb[0], nb1 = g->nb[1], nb2 = g->nb[2];
     const int b0 = bin / (nb1 * nb2), b1 = (bin / nb2) % nb1, b2 = bin % nb2;
-    const int r0 = g.reach[0], r1 = g.reach[1], r2 = g.reach[2];
+    const int r0 = g->reach[0], r1 = g->reach[1], r2 = g->reach[2];
+    float big = 0.f;
+    for (int c = 0; c < 3; ++c)
+        big = fmaxf(big, float(fabs(g->h[c]) + fabs(g->h[3 + c]) + fabs(g->h[6 + c])) * 1.000001f);
+    const float rcl = float(b.rcl), rclf2 = float(b.rcl2), u = 0x1p-24f;
+    const float e = 1.7320509f * (4.f + 2.f * float(max(r0, max(r1, r2)))) * u * big;
+    const float delta = 1.01f * (2.f * rcl * e + e * e) + 12.f * u * rclf2;
+    const float lo2 = rclf2 - delta, hi2 = rclf2 + delta;
     const double rcl2 = b.rcl2;
-    const int ccap = b.ccap;
+    const int ccap = b.ccap, natoms = b.N;
+    const bool far = cp(b.skst + slot)->far != 0;
     int cnt = 0;
     bool bad_shift = false;
+    // records lo..hi-1 in bin order, seen from bin shift (m0, m1, m2)
+    auto scan = [&](int lo, int hi, int m0, int m1, int m2) {
+        const float sx = float(double(m0) * g->h[0] + double(m1) * g->h[3] + double(m2) * g->h[6]);
+        const float sy = float(double(m0) * g->h[1] + double(m1) * g->h[4] + double(m2) * g->h[7]);
+        const float sz = float(double(m0) * g->h[2] + double(m1) * g->h[5] + double(m2) * g->h[8]);
+        constexpr int U = 4;
+        for (int p0 = lo + U * half; p0 - U * half < hi; p0 += 2 * U) {
+            float4 a[U];
+            float rr[U];
+            int j[U], imj[U];
+            bool in[U];
+#pragma unroll
+            for (int w = 0; w < U; ++w) a[w] = load4(bp, min(p0 + w, hi - 1));
+#pragma unroll
+            for (int w = 0; w < U; ++w) {
+                const float dx = (a[w].x - me.x) + sx, dy = (a[w].y - me.y) + sy, dz = (a[w].z - me.z) + sz;
+                rr[w] = dx * dx + dy * dy + dz * dz;
+                j[w] = nbr_j(__float_as_uint(a[w].w));
+                const bool self = int(j[w] == i) & int((m0 | m1 | m2) == 0);
+                in[w] = int(p0 + w < hi) & int(rr[w] < hi2) & int(!self);
+            }
+            if (far)  // uniform over the block; the record's own image fields wrap
+#pragma unroll
+                for (int w = 0; w < U; ++w) imj[w] = img[in[w] ? j[w] : i];
+            uint32_t ent[U];
+            int own = 0;
+#pragma unroll
+            for (int w = 0; w < U; ++w) {
+                if (!in[w]) continue;
+                int n[3] = {m0, m1, m2};
+                for (int q = 0; q < 3; ++q)
+                    n[q] += img_n(im, q) -
+                            (far ? img_n(imj[w], q) : 3 - int((__float_as_uint(a[w].w) >> (20 + 4 * q)) & 15u));
+                if (!(rr[w] < lo2)) {  // rare: FP32 cannot tell
+                    const double4 rj = load4(R, j[w]);
+                    double h[9], d[3];
+                    for (int q = 0; q < 9; ++q) h[q] = g->h[q];
+                    in[w] = exact_r2(ri, rj.x, rj.y, rj.z, h, n[0], n[1], n[2], d) < rcl2;
+                }
+                if (in[w] && (abs(n[0]) > CFNEB_MAX_SHIFT || abs(n[1]) > CFNEB_MAX_SHIFT || abs(n[2]) > CFNEB_MAX_SHIFT)) {
+                    bad_shift = true;
+                    in[w] = false;
+                }
+                ent[w] = pack_nbr(j[w], n[0], n[1], n[2]);
+                own += in[w] ? 1 : 0;
+            }
+            const int other = dpp_i32<0xB1>(own);  // (the pair takes every branch together)
+            int pos = cnt + (half ? other : 0);
+            cnt += own + other;
+#pragma unroll
+            for (int w = 0; w < U; ++w) {
+                if (!in[w]) continue;
+                if (pos < ccap) cand[cand_at(ccap, i, pos)] = ent[w];
+                ++pos;
+            }
+        }
+    };
+    // the bins b2 - r2 .. b2 + r2 of a row that lie in one cell are one run of records
+    int unused, mlo, mhi;
+    wrap_bin(b2 - r2, nb2, unused, mlo);
+    wrap_bin(b2 + r2, nb2, unused, mhi);
     for (int dx = -r0; dx <= r0; ++dx) {
         int a0, m0;
         wrap_bin(b0 + dx, nb0, a0, m0);
         for (int dy = -r1; dy <= r1; ++dy) {
             int a1, m1;
             wrap_bin(b1 + dy, nb1, a1, m1);
-            for (int dz = -r2; dz <= r2; ++dz) {
-                int a2, m2;
-                wrap_bin(b2 + dz, nb2, a2, m2);
-                const int row = (a0 * nb1 + a1) * nb2 + a2;
-                const int hi = min(start[row + 1], b.N);
-                for (int p = start[row]; p < hi; ++p) {
-                    const int j = nbr_j(bp[p].code), imj = img[j];
-                    const int n0 = m0 + img_n(im, 0) - img_n(imj, 0);
-                    const int n1 = m1 + img_n(im, 1) - img_n(imj, 1);
-                    const int n2 = m2 + img_n(im, 2) - img_n(imj, 2);
-                    if (j == i && n0 == 0 && n1 == 0 && n2 == 0) continue;
-                    const double4 rj = load4(R, j);
-                    double d[3];
-                    if (!(exact_r2(ri, rj.x, rj.y, rj.z, h, n0, n1, n2, d) < rcl2)) continue;
-                    if (abs(n0) > CFNEB_MAX_SHIFT || abs(n1) > CFNEB_MAX_SHIFT || abs(n2) > CFNEB_MAX_SHIFT) {
-                        bad_shift = true;
-                        continue;
-                    }
-                    if (cnt < ccap) cand[cand_at(ccap, i, cnt)] = pack_nbr(j, n0, n1, n2);
-                    ++cnt;
-                }
+            const int row = (a0 * nb1 + a1) * nb2;
+            for (int m2 = mlo; m2 <= mhi; ++m2) {
+                const int z0 = max(b2 - r2 - m2 * nb2, 0), z1 = min(b2 + r2 - m2 * nb2, nb2 - 1);
+                scan(start[row + z0], min(start[row + z1 + 1], natoms), m0, m1, m2);
             }
         }
     }
-    b.ncand[size_t(slot) * b.N + i] = min(cnt, ccap);
+    if (half == 0) b.ncand[size_t(slot) * b.N + i] = min(cnt, ccap);
     if (bad_shift) set_error(st, CFNEB_ECELL);
     if (cnt > ccap) set_error(st, CFNEB_ENEIGH);
 }
@@ -945,6 +1009,7 @@ k_cand(BatchDev bd, int all_images)
     __shared__ CandLds lds[CFNEB_WAVES];
     if (*rebuild_flag(bd) == 0) return;  // no image rebuilds this step
     Item it;
+    int others = 0;
     ItemLoopRO loop(bd, KIND_CAND, all_images);
     while (loop.next(it)) {
         const BandDev b = band_ro(bd, it.band);
@@ -955,8 +1020,7 @@ k_cand(BatchDev bd, int all_images)
         if (!sk->rebuild) continue;
         const cmem<ImageGeom>* g = cp(b.geom + slot);
         if (!cand_by_groups(g, sk)) {
-            const int i = it.tile * CFNEB_TILE_CAND + threadIdx.x;
-            if (int(threadIdx.x) < CFNEB_TILE_CAND && i < b.N) cand_item(b, b.st, slot, i);
+            others = 1;
             continue;
         }
         // the tiles of an image share its groups evenly, in runs
@@ -967,6 +1031,20 @@ k_cand(BatchDev bd, int all_images)
         // (the waves take turns at the first group, so an uneven share goes round)
         const int turn = (wave + it.tile) & (CFNEB_WAVES - 1);
         for (int q = it.tile * per + turn; q < end; q += CFNEB_WAVES) cand_group(b, b.st, g, slot, q, gz, lds[wave]);
+    }
+    // the images that groups do not serve, in a walk of their own: inside the one above their
+    // code costs it scalar registers (114 -> 116 us where no image takes it)
+    if (uni(others) == 0) return;  // uniform over the wave (no barrier follows)
+    ItemLoopRO again(bd, KIND_CAND, all_images);
+    while (again.next(it)) {
+        const BandDev b = band_ro(bd, it.band);
+        const cmem<BandState>* st = cp(b.st);
+        if (band_stopped(st)) continue;
+        const int slot = st->slot[it.image];
+        const cmem<SkinState>* sk = cp(b.skst + slot);
+        if (!sk->rebuild || cand_by_groups(cp(b.geom + slot), sk)) continue;
+        const int p = it.tile * CFNEB_TILE_CAND + (int(threadIdx.x) >> 1);
+        if (p < b.N) cand_item(b, b.st, slot, p, int(threadIdx.x) & 1);
     }
 }
 

@@ -1,0 +1,38 @@
+"""The candidate scan of one thread per atom (cells narrower than the cutoff, images more than
+three cells away), without a skin, so the list is the neighbour set: pairs within 1e-7 of the
+cutoff, which FP32 cannot tell apart, one and many periods of the cell, ragged tiles.  The
+oracle's sets, bit for bit."""
+import numpy as np
+import pytest
+
+from gpu_cases import sort_entries
+
+pytestmark = pytest.mark.gpu
+
+RC = 2.5
+A = RC / 3.0  # a cubic lattice where the (2, 2, 1) shell lies at the cutoff
+
+
+@pytest.mark.parametrize("cells,image", [((2, 9, 8), 0), ((1, 1, 70), 0), ((1, 5, 8), 0), ((2, 2, 64), 0), ((8, 9, 7), 5),
+                                         ((7, 7, 7), -6), ((2, 8, 9), 5), ((9, 1, 33), 4)])
+def test_pairs_at_the_cutoff(cells, image):
+    import oracle
+    import torch
+    from paper_2510_16721_amd import cfneb
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    rng = np.random.default_rng(sum(cells) + image)
+    g = np.stack(np.meshgrid(*[np.arange(c) for c in cells], indexing="ij"), -1).reshape(-1, 3)
+    g = g[rng.permutation(len(g))]
+    h = np.diag(np.array(cells) * A)
+    pos = (g + 0.3) * A + rng.uniform(-1e-7, 1e-7, g.shape) + np.array([image, 0, -image]) @ h
+    p = cfneb.default_params(cfneb.CFNEB_LJ, n_images=3, max_images=3, lj_rc=RC, nbr_skin=0.0, nbr_cap=200)
+    band = cfneb.Band(p, pos, h, pos + 0.01, h @ np.array([[1.0, 0.0, 0.0], [0.02, 1.0, 0.0], [0.0, -0.01, 1.0]]))
+    for k in (0, 2):
+        img = band.image(k)
+        cnt, ent = band.neighbours(k)
+        ref = oracle.nlist(img["R"], img["h"], RC)
+        assert [int(c) for c in cnt] == [len(r) for r in ref]
+        for i in range(len(pos)):
+            np.testing.assert_array_equal(sort_entries(ent[i]), ref[i])
+    band.close()
