@@ -106,20 +106,21 @@ bool make_layout(const cfneb_params* p, int64_t n_atoms, int max_images, Layout*
     return true;
 }
 
-// Lanes sharing an atom in the LJ force kernel, a property of the band: from the
-// table that tune_lanes.py measures (fastest lane count of a band stepped alone, by
-// atoms x moving images), or CFNEB_LJ_LANES.
-int lj_lanes_for(long long atoms, int images)
+// Lanes sharing an atom in the LJ force kernel, a property of the band: from the tables
+// that tune_lanes.py measures (bands by atoms x moving images, a count that also does for a
+// full batch; relaxations by atoms, the fastest alone), or CFNEB_LJ_LANES.
+int lj_lanes_for(long long atoms, int images, bool fp64, bool relax)
 {
     const char* v = std::getenv("CFNEB_LJ_LANES");
     if (v) {
         const int k = std::atoi(v);
         if (k == 1 || k == 2 || k == 4 || k == 8 || k == 16 || k == 32) return k;
     }
+    // (the last row of each table is open-ended)
+    const LjLanesEntry* e = relax ? (fp64 ? kLjLanesRelaxFp64 : kLjLanesRelax) : fp64 ? kLjLanesFp64 : kLjLanesTable;
     const long long work = atoms * (images - 2);
-    for (const auto& e : kLjLanesTable)
-        if (work <= e.max_atom_images) return e.lanes;
-    return 1;
+    while (work > e->max_atom_images) ++e;
+    return e->lanes;
 }
 
 // Grids of a band table, bounded by the most items its bands can hold.
@@ -252,7 +253,7 @@ void fill_dev(cfneb_band* b, void* ws, const double* h0, int relax)
     d.rcl = d.rc + d.skin;
     d.rcl2 = d.rcl * d.rcl;
     d.lj_eps = p->lj_eps;
-    d.lj_lanes = lj_lanes_for(L.N, p->n_images);
+    d.lj_lanes = lj_lanes_for(L.N, p->n_images, d.fp64 != 0, relax != 0);
     d.lj_tile = std::max(CFNEB_TILE / d.lj_lanes, lj_least_tile(L.N));
     d.ntF = p->potential == CFNEB_LJ ? (L.N + d.lj_tile - 1) / d.lj_tile : L.ntA;
     d.lj_sig2 = p->lj_sigma * p->lj_sigma;
