@@ -4,8 +4,8 @@
 //   X      [slot][3][ld]  FP64  generalized coordinates: rows 0..N-1 = R~ (SoA),
 //                               rows N..N+2 = the three rows of c_f B
 //   V      [2][slot][3][ld] FP64 FIRE velocities, ping-pong (vcur selects)
-//   R      [slot][ld]     32 B  Cartesian positions R = R~ D of the last evaluation
-//   S      [slot][ld]     16 B  FP32 LJ bands: fractional coordinates of R in the
+//   R      [slot][ld]     24 B  Cartesian positions R = R~ D of the last evaluation
+//   S      [slot][ld]     12 B  FP32 LJ bands: fractional coordinates of R in the
 //                               image's cell, wrapped to [0, 1), as 32-bit fixed point
 //   F      [slot][3][ld]  T     Cartesian forces (T = float, or double for FP64 bands)
 //   FN     [slot][3][ld]  FP64  NEB force (only when recording is on)
@@ -18,7 +18,7 @@
 //   ncnt   [slot][N]      int   neighbour count (may exceed cap: overflow)
 //   dvec   [slot][cap][N] T4    Tersoff: bond vector and length (bonds past the fourth)
 //   bo     [slot][cap][N] T2    Tersoff: b_ij and db/dzeta (same)
-//   P      [slot][ccap][N] T4   Tersoff: dU_i/dr^ij per candidate (zero if not a bond)
+//   P      [slot][ccap][N] 3 T  Tersoff: dU_i/dr^ij per candidate (zero if not a bond)
 //   geom / scal [slot]          per-image 3x3 geometry and reduced scalars
 //   partial buffers             fixed-order block partials of every reduction
 //   state                       band scalars (FIRE, slot table, flags)
@@ -36,10 +36,11 @@
 
 #define CFNEB_MAX_IMAGES 64
 #define CFNEB_TILE 256           // threads per block of every streaming kernel
-// Atoms per item of the candidate scan: in a dense system about ten groups of bins, two
-// or three a wave, so that bands of a few 10^5 atom-images still give every SIMD several
-// waves (LJ, 11 images of 16,383 atoms: 251 us with items of 256 bins, 148 us with 96
-// atoms; 22 images of 97,555: 821 us with 192 atoms, 923 us with 96).
+// Atoms per item of the candidate scan (its general path gives an atom two of a block's
+// threads): in a dense system about ten groups of bins, two or three a wave, so that bands of
+// a few 10^5 atom-images still give every SIMD several waves.  A build with items of 96 | 128 |
+// 192 | 256 atoms: 22 images of 97,555 LJ atoms 1,134 | 1,133 | 1,103 | 1,105 us (no skin), 9 of
+// 16,383 111 | 117 | 112 | 142, one of 16,383 58 | 68 | 89 | 116, 7 of 2,047 84 | 70 | 91 | 115.
 #define CFNEB_TILE_CAND 128
 #define CFNEB_TILE4 1024         // rows (atoms) of a streaming item with 4 per thread
 // Bands of up to this many atoms have their positions, skin test and bins done by one
@@ -623,7 +624,7 @@ struct Launch {
     BatchDev bd;
     unsigned g[NKIND];
     // grid of the force kernels (LJ pair kernel, the two Tersoff kernels): the
-    // persistent grid g[KIND_ATOM] or one block per atom tile of the largest item
+    // persistent grid g[KIND_TS] (= g[KIND_LJ1], g[KIND_LJK]) or one block per item of the largest item
     // count (g_force_tile), where the hardware hands the last tiles to whichever
     // slots free first; chosen by timing before the step graphs are captured
     unsigned g_force, g_force_tile;

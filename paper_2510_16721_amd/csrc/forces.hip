@@ -27,7 +27,8 @@ namespace cfneb {
 // is the fixed butterfly sum of its lanes, energy and virial go into the wave sums.
 // An item is 256 / K atoms, so more lanes are more blocks: a band of a few thousand
 // atom-images fills the chip (255 atoms, 5 moving images, FP64: 5 blocks of one lane an
-// atom 32.5 us, 8.7 us with 16; lj_lanes_table.h has the times of every size).
+// atom 35.5 us, 10.9 us with 8; lj_lanes_table.h has the times of every size, and what a
+// full batch pays for it).
 //
 // FP64-record path (FP64 bands, narrow cells): the inclusion test decides on the
 // exact FP64 r^2 (every operation rounded on its own): the separation d is formed in FP64 (a candidate without a lattice shift, most
@@ -176,11 +177,12 @@ __device__ inline uint4 ld_u96(const void* base, uint32_t off)
 // rounding error, a strain of ~1e-7 that the virial sum multiplies by the stiffness).
 // The FP32 r^2 settles the pair outside [r2lo, r2hi); inside that band the exact FP64
 // test runs on the FP64 positions.
-// Bound by two units at once (97,555 atoms x 22 images, 8 % under either): 57 vector
-// instructions a pair fill 92 % of the issue slots, the position gathers take 91 % of the
+// Bound by two units at once (97,555 atoms x 22 images): at 2.4 GHz the 57 vector
+// instructions a pair fill 83 % of the issue slots and the position gathers 82 % of the
 // cache's cycles (a lane's line each).  The next four entries load during this batch, and a
 // pair outside rc is dropped by one select: 341 -> 338 us there; in a batch of 64 bands of
-// up to 32,000 atoms 224 -> 206 us a step here and 202 -> 180 us with several lanes.
+// up to 32,000 atoms 224 -> 206 us a step here and 202 -> 180 us with several lanes (216 and
+// 141 with the lanes that a full batch bears).
 template <int K>
 __device__ void lj_fixed_item(const BandDev& b, BandState* st, int slot, int tile)
 {

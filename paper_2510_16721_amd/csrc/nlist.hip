@@ -727,11 +727,12 @@ __device__ void cand_item(const BandDev& b, BandState* st, int slot, int p, int 
 // of the group's atoms in turn, 64 records are tested at a time, one per lane, and the
 // lanes inside append their entries (ballot prefix).  A thread per atom instead walks its
 // stencil as a serial chain of loads with every test and append diverging inside the wave.
-// Bound by vector issue (69 % of the slots) and the scattered stores of the entries.
-// Building the lists of 22 images of 97,555 LJ atoms: 3,180 us with a thread per atom, 850 us
-// in groups, 720 us with lane sets held as scalar masks (a compare a test instead of three
-// instructions), the record loop not unrolled (ten copies of it overran the instruction
-// cache) and images added as fields that cannot carry.
+// Bound by vector issue (62 % of the slots at 2.4 GHz on the lattice) and the scattered stores
+// of the entries.  Building the lists of 24 images of 97,555 LJ atoms: 4,960 us with a thread
+// per atom, 1,360 us this way (the perfect lattice 4,780 and 1,190).  Of the way there, in means
+// over steps on which some images rebuild: lane sets held as scalar masks (a compare a test
+// instead of three instructions) 489 -> 446 us, the record loop not unrolled (ten copies of it
+// overran the instruction cache) 432, images added as fields that cannot carry 416.
 //
 // Distances are FP32 between wrapped positions: each component is within 10 2^-24 of the
 // largest coordinate L (1 for the rounding of either position, 2 for the shift from the
@@ -741,10 +742,12 @@ __device__ void cand_item(const BandDev& b, BandState* st, int slot, int p, int 
 // (97,555 LJ atoms | request of 16,383: runs of 2 bins 17 | 24 % slower, of 3 5 % faster | 7 %
 // slower; stages of 384 records 9 | 7 % slower; one atom to a record read 5 % slower, three or
 // four 5 to 8 %.)  Full-width bins hold a quarter of the atoms (two or three), so their runs
-// are longer: 73,728 carbon atoms of graphite x 12 images 390 us a build in runs of 4, 325 of
-// 12; 39,303 of diamond x 7 images 64 | 62 us mean a step; below 16,384 atoms the groups are
-// too few for that (2,743 x 11 images 15.3 us in runs of 8, 18.1 of 12).  A row's bins are
-// shared evenly among its groups.
+// are longer: 12 bins from 16,385 atoms on, 8 below.  Which is better goes by how a row's
+// bins divide as much as by size (a row's bins are shared evenly among its groups); carbon,
+// us a build with 8 | 12: diamond of 2,743 atoms x 11 images 44 | 49, 13,823 x 1 40 | 38,
+// 13,823 x 22 99 | 101, 17,575 x 1 41 | 40, 46,655 x 1 50 | 40, 46,655 x 10 144 | 130,
+// 63,999 x 7 133 | 138, 85,183 x 7 174 | 211, 97,335 x 5 147 | 133; graphite of 73,728 x 12
+// 325 with 12, 390 with 4.
 #define CAND_RUN 4
 #define CAND_RUN_SPARSE 12
 #define CAND_RUN_SMALL 8
@@ -1033,7 +1036,7 @@ k_cand(BatchDev bd, int all_images)
         for (int q = it.tile * per + turn; q < end; q += CFNEB_WAVES) cand_group(b, b.st, g, slot, q, gz, lds[wave]);
     }
     // the images that groups do not serve, in a walk of their own: inside the one above their
-    // code costs it scalar registers (114 -> 116 us where no image takes it)
+    // code costs it scalar registers (two LJ bands, no image taking it: 113.6 -> 115.6 us)
     if (uni(others) == 0) return;  // uniform over the wave (no barrier follows)
     ItemLoopRO again(bd, KIND_CAND, all_images);
     while (again.next(it)) {

@@ -320,9 +320,9 @@ __device__ void ts_atom_regs(const TersoffT<T>& P, const vec4_t<T> (&bond)[MAXB]
 // lane e of the group has bond e (d, cid) and sees the others in increasing order.  One
 // lane walking them through memory held its whole wave, and in a small band the launch: a
 // chain of cnt^2 loads (a 511-atom vacancy hop, whose hopping atom has such a shell:
-// 36 us a launch, 14 us this way; 98,304 atoms,
-// 22 images on their way to diamond: a step 505 -> 406 us).  i, cnt: the group's atom and its bonds (0: idle group);
-// most: the largest cnt of the wave.
+// 36 us a launch, 14 us this way; 98,304 atoms, 22 images on their way to diamond: a step
+// 505 -> 406 us).  i, cnt: the group's atom and its bonds (0: idle group); most: the largest
+// cnt of the wave.
 template <typename T, int G>
 __device__ void ts_atom_group(const TersoffT<T>& P, const vec4_t<T>& de, int cid, gmem<P3<T>>* Pout, size_t N, int i,
                               int cnt, int most, double* acc)
