@@ -31,12 +31,12 @@ namespace cfneb {
 // full batch pays for it).
 //
 // FP64-record path (FP64 bands, narrow cells): the inclusion test decides on the
-// exact FP64 r^2 (every operation rounded on its own): the separation d is formed in FP64 (a candidate without a lattice shift, most
-// of them in a large cell, skips the shift arithmetic, which adds an exact zero), and
-// its FP32 square, within 3e-7 of r^2 relative, settles every pair outside a 1e-6
-// band around rc^2; only pairs inside the band square d in FP64.  The virial of a
-// pair is symmetric (f parallel to d): six FP32 components, added to the FP64 sums once
-// per batch of four candidates.
+// exact FP64 r^2 (every operation rounded on its own): the separation d is formed in FP64
+// (a candidate without a lattice shift, most of them in a large cell, skips the shift
+// arithmetic, which adds an exact zero), and its FP32 square, within 3e-7 of r^2 relative,
+// settles every pair outside a 1e-6 band around rc^2; only pairs inside the band square d in
+// FP64.  The virial of a pair is symmetric (f parallel to d): six FP32 components, added to
+// the FP64 sums once per batch of four candidates.
 __device__ inline void separation(const double* ri, const double4& rj, const double* h, uint32_t ent,
                                   double* d)
 {
@@ -177,9 +177,9 @@ __device__ inline uint4 ld_u96(const void* base, uint32_t off)
 // rounding error, a strain of ~1e-7 that the virial sum multiplies by the stiffness).
 // The FP32 r^2 settles the pair outside [r2lo, r2hi); inside that band the exact FP64
 // test runs on the FP64 positions.
-// Bound by two units at once (97,555 atoms x 22 images): at 2.4 GHz the 57 vector
-// instructions a pair fill 83 % of the issue slots and the position gathers 82 % of the
-// cache's cycles (a lane's line each).  The next four entries load during this batch, and a
+// Bound by two units at once (97,555 atoms x 22 images, 333 to 357 us on different cards): at
+// 2.4 GHz the 57 vector instructions a pair fill 80 to 84 % of the issue slots and the position
+// gathers (a lane's line each) 79 to 82 % of the cache's cycles.  The next four entries load during this batch, and a
 // pair outside rc is dropped by one select: 341 -> 338 us there; in a batch of 64 bands of
 // up to 32,000 atoms 224 -> 206 us a step here and 202 -> 180 us with several lanes (216 and
 // 141 with the lanes that a full batch bears).
