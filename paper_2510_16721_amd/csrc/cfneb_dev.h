@@ -112,7 +112,8 @@ struct SkinState {
     int valid;                 // a candidate list exists for this slot
     int rebuild;               // this step rebuilds it
     int held;                  // rebuild, set aside while the force grid is tuned
-    int far;                   // an atom lay more than 3 cells away at the last build
+    short far;                 // an atom lay more than 3 cells away at the last build
+    short uneven;              // a share of the candidate scan's groups had too many atoms
 };
 
 struct ImageScal {

@@ -203,7 +203,7 @@ __device__ inline bool skin_decision(const BatchDev& bd, const BandDev& b, int s
             sk.href[q] = g.h[q];
             sk.hrefinv[q] = g.hinv[q];
         }
-        sk.far = 0;
+        sk.far = sk.uneven = 0;
         sk.valid = 1;
         *rebuild_flag(bd) = 1;
     }
@@ -279,6 +279,53 @@ __device__ inline BinAtom bin_record(const ImageGeom& g, const double4& ri, int 
     return a;
 }
 
+// Half-width bins go in runs of four: two are 17 % slower on 97,555 LJ atoms and 24 % on a
+// request of 16,383, three 5 % faster and 7 % slower.  Full-width bins hold a quarter of the
+// atoms (two or three), so their runs are longer: 12 bins from 16,385 atoms on, 8 below.
+// Which is better goes by how a row's bins divide as much as by size (a row's bins are shared
+// evenly among its groups); carbon, us a build with 8 | 12: diamond of 2,743 atoms x 11 images
+// 44 | 49, 13,823 x 1 40 | 38, 13,823 x 22 99 | 101, 17,575 x 1 41 | 40, 46,655 x 1 50 | 40,
+// 46,655 x 10 144 | 130, 63,999 x 7 133 | 138, 85,183 x 7 174 | 211, 97,335 x 5 147 | 133;
+// graphite of 73,728 x 12 325 with 12, 390 with 4.
+#define CAND_RUN 4
+#define CAND_RUN_SPARSE 12
+#define CAND_RUN_SMALL 8
+
+// How the candidate scan shares out an image's bins: groups of up to `run` bins of a row along
+// the third axis (gz to a row), `per` consecutive groups to each of its tiles.
+struct CandShares {
+    int gz, total, per;
+};
+template <typename G>
+__device__ inline CandShares cand_shares(const G* g, int N)
+{
+    const int run = g->sub > 1 ? CAND_RUN : N > 16384 ? CAND_RUN_SPARSE : CAND_RUN_SMALL;
+    const int tiles = (N + CFNEB_TILE_CAND - 1) / CFNEB_TILE_CAND;
+    CandShares c;
+    c.gz = (g->nb[2] + run - 1) / run;
+    c.total = g->nb[0] * g->nb[1] * c.gz;
+    c.per = (c.total + tiles - 1) / tiles;
+    return c;
+}
+// Shares of more than three times the mean number of atoms (clusters, wires: most bins are
+// empty and the others in a few rows) would hold a few waves while the rest of the chip waits;
+// such images take the scan that shares out atoms (cand_item).  All threads of the block, the
+// bins' starts in place.  A ball of 16,000 LJ atoms in twice its lattice's edge, one image, a
+// step that builds its list: 945 us by groups, 223 us that way (463 before there were groups).
+// The shares of a crystal reach 1.8 times the mean at most.
+template <typename S>
+__device__ inline void flag_uneven(const BandDev& b, const ImageGeom& g, int slot, const S* start)
+{
+    const CandShares c = cand_shares(&g, b.N);
+    auto first_bin = [&](int q) {
+        const int row = q / c.gz;
+        return row * g.nb[2] + (q - row * c.gz) * g.nb[2] / c.gz;
+    };
+    for (int q = int(threadIdx.x) * c.per; q < c.total; q += int(blockDim.x) * c.per)
+        if (int(start[first_bin(min(q + c.per, c.total))]) - int(start[first_bin(q)]) > 3 * CFNEB_TILE_CAND)
+            b.skst[slot].uneven = 1;
+}
+
 // The bins of one image by one block of 1024 threads: counts, then starts, and the ids of
 // each bin in LDS (16 bits each: at most CFNEB_BIN_IMAGE atoms).  Four atoms a thread at a
 // time, so the loads of a round are in flight together.
@@ -335,6 +382,7 @@ __device__ void bins_of_image(const BandDev& b, const ImageGeom& g, int slot, un
         gstart[nbins] = N;
     }
     __syncthreads();
+    flag_uneven(b, g, slot, start);
     for (int i0 = t; i0 < N; i0 += 1024 * Q) {
         int bin[Q], rank[Q];
 #pragma unroll
@@ -516,6 +564,8 @@ __device__ void bin_scan_item(const BandDev& b, int slot)
         __syncthreads();
     }
     if (t == 0) start[nbins] = carry;
+    __syncthreads();
+    flag_uneven(b, b.geom[slot], slot, start);
 }
 
 __global__ void __launch_bounds__(1024) k_bin_scan(BatchDev bd, int all_images)
@@ -596,8 +646,8 @@ __device__ inline void wrap_bin(int v, int nb, int& a, int& m)
 
 // Candidates of the atom of record p (bin order), two neighbouring lanes: every (j, n) within
 // rcl in stencil order; R_ref = R.  Serves images whose stencil spans more than one neighbouring
-// cell (cells narrower than rcl) or with atoms more than three cells away, where 4-bit
-// lattice images could wrap.  Each lane takes four of eight records at a time.  FP32 between
+// cell (cells narrower than rcl), with atoms more than three cells away, where 4-bit lattice
+// images could wrap, or whose atoms crowd a share of the groups (flag_uneven).  Each lane takes four of eight records at a time.  FP32 between
 // wrapped positions decides outside a band around rcl^2 (a component: 1 2^-24 of the largest
 // coordinate L for the rounding of either position and for their difference, reach for that of
 // the shift, 1 + reach for the sum), the exact FP64 test inside it; lattice images come with
@@ -739,18 +789,8 @@ __device__ void cand_item(const BandDev& b, BandState* st, int slot, int p, int 
 // box's middle, at most 5 for sums no larger than the stencil; L is at least rcl here), so
 // FP32 r^2 decides outside a band around rcl^2 and the exact FP64 test inside it: the
 // list holds exactly the pairs that the FP64 test gives.
-// (97,555 LJ atoms | request of 16,383: runs of 2 bins 17 | 24 % slower, of 3 5 % faster | 7 %
-// slower; stages of 384 records 9 | 7 % slower; one atom to a record read 5 % slower, three or
-// four 5 to 8 %.)  Full-width bins hold a quarter of the atoms (two or three), so their runs
-// are longer: 12 bins from 16,385 atoms on, 8 below.  Which is better goes by how a row's
-// bins divide as much as by size (a row's bins are shared evenly among its groups); carbon,
-// us a build with 8 | 12: diamond of 2,743 atoms x 11 images 44 | 49, 13,823 x 1 40 | 38,
-// 13,823 x 22 99 | 101, 17,575 x 1 41 | 40, 46,655 x 1 50 | 40, 46,655 x 10 144 | 130,
-// 63,999 x 7 133 | 138, 85,183 x 7 174 | 211, 97,335 x 5 147 | 133; graphite of 73,728 x 12
-// 325 with 12, 390 with 4.
-#define CAND_RUN 4
-#define CAND_RUN_SPARSE 12
-#define CAND_RUN_SMALL 8
+// (97,555 LJ atoms | request of 16,383: stages of 384 records 9 | 7 % slower; one atom to a
+// record read 5 % slower, three or four 5 to 8 %.)
 #define CAND_STAGE 512
 #define CAND_SEGS 64
 struct CandSeg {
@@ -803,7 +843,7 @@ __device__ inline void wave_lds_fence()
 __device__ inline bool cand_by_groups(const cmem<ImageGeom>* g, const cmem<SkinState>* sk)
 {
     const int r = g->sub;
-    return int(sk->far == 0) & int(g->reach[0] == r) & int(g->reach[1] == r) & int(g->reach[2] == r) &
+    return int((sk->far | sk->uneven) == 0) & int(g->reach[0] == r) & int(g->reach[1] == r) & int(g->reach[2] == r) &
            int(g->nb[0] >= r) & int(g->nb[1] >= r) & int(g->nb[2] >= r);
 }
 
@@ -1027,13 +1067,11 @@ k_cand(BatchDev bd, int all_images)
             continue;
         }
         // the tiles of an image share its groups evenly, in runs
-        const int run = g->sub > 1 ? CAND_RUN : b.N > 16384 ? CAND_RUN_SPARSE : CAND_RUN_SMALL;
-        const int gz = (g->nb[2] + run - 1) / run, total = g->nb[0] * g->nb[1] * gz;
-        const int tiles = kind_tiles(b, KIND_CAND), per = (total + tiles - 1) / tiles;
-        const int end = min((it.tile + 1) * per, total), wave = uni(int(threadIdx.x) >> 6);
+        const CandShares c = cand_shares(g, b.N);
+        const int end = min((it.tile + 1) * c.per, c.total), wave = uni(int(threadIdx.x) >> 6);
         // (the waves take turns at the first group, so an uneven share goes round)
         const int turn = (wave + it.tile) & (CFNEB_WAVES - 1);
-        for (int q = it.tile * per + turn; q < end; q += CFNEB_WAVES) cand_group(b, b.st, g, slot, q, gz, lds[wave]);
+        for (int q = it.tile * c.per + turn; q < end; q += CFNEB_WAVES) cand_group(b, b.st, g, slot, q, c.gz, lds[wave]);
     }
     // the images that groups do not serve, in a walk of their own: inside the one above their
     // code costs it scalar registers (two LJ bands, no image taking it: 113.6 -> 115.6 us)

@@ -1,7 +1,7 @@
-"""The candidate scan of one thread per atom (cells narrower than the cutoff, images more than
-three cells away), without a skin, so the list is the neighbour set: pairs within 1e-7 of the
-cutoff, which FP32 cannot tell apart, one and many periods of the cell, ragged tiles.  The
-oracle's sets, bit for bit."""
+"""The candidate scan that shares out atoms (cells narrower than the cutoff, images more than
+three cells away, balls of atoms in vacuum), without a skin, so the list is the neighbour set:
+pairs within 1e-7 of the cutoff, which FP32 cannot tell apart, one and many periods of the cell,
+ragged tiles.  The oracle's sets, bit for bit."""
 import numpy as np
 import pytest
 
@@ -35,4 +35,33 @@ def test_pairs_at_the_cutoff(cells, image):
         assert [int(c) for c in cnt] == [len(r) for r in ref]
         for i in range(len(pos)):
             np.testing.assert_array_equal(sort_entries(ent[i]), ref[i])
+    band.close()
+
+
+@pytest.mark.parametrize("n,edge,images", [(2500, 2.2, 0), (2500, 2.2, 3), (4097, 2.0, 0), (9001, 1.7, 2), (36865, 2.0, 1)])
+def test_balls_in_vacuum(n, edge, images):
+    # all atoms in a few of the rows of bins, with each of the three ways that bins are made;
+    # written in lattice images up to `images` cells away
+    import oracle
+    import torch
+    from paper_2510_16721_amd import cfneb
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    rng = np.random.default_rng(n + images)
+    m = int(np.ceil((n / 0.5) ** (1.0 / 3.0))) + 1
+    g = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    g = g[np.argsort(np.linalg.norm(g - 0.5 * (m - 1), axis=1), kind="stable")[:n]]
+    g = g[rng.permutation(n)]
+    L = edge * A * n ** (1.0 / 3.0)
+    h = np.diag([L, L, L]) + np.array([[0, 0, 0], [0.05, 0, 0], [-0.03, 0.04, 0]]) * L
+    pos = (g - 0.5 * m) * A + 0.5 * h.sum(0) + rng.uniform(-1e-7, 1e-7, g.shape)
+    pos = pos + rng.integers(-images, images + 1, g.shape) @ h
+    p = cfneb.default_params(cfneb.CFNEB_LJ, n_images=3, max_images=3, lj_rc=RC, nbr_skin=0.0, nbr_cap=200, cell_filter=0)
+    band = cfneb.Band(p, pos, h, pos + 0.01, h)
+    img = band.image(2)
+    cnt, ent = band.neighbours(2)
+    ref = oracle.nlist(img["R"], img["h"], RC)
+    assert [int(c) for c in cnt] == [len(r) for r in ref]
+    for i in range(n):
+        np.testing.assert_array_equal(sort_entries(ent[i]), ref[i])
     band.close()
