@@ -647,11 +647,12 @@ __device__ inline void wrap_bin(int v, int nb, int& a, int& m)
 // Candidates of the atom of record p (bin order), two neighbouring lanes: every (j, n) within
 // rcl in stencil order; R_ref = R.  Serves images whose stencil spans more than one neighbouring
 // cell (cells narrower than rcl), with atoms more than three cells away, where 4-bit lattice
-// images could wrap, or whose atoms crowd a share of the groups (flag_uneven).  Each lane takes four of eight records at a time.  FP32 between
-// wrapped positions decides outside a band around rcl^2 (a component: 1 2^-24 of the largest
-// coordinate L for the rounding of either position and for their difference, reach for that of
-// the shift, 1 + reach for the sum), the exact FP64 test inside it; lattice images come with
-// the records unless the image's atoms are far.
+// images could wrap, or whose atoms crowd a share of the groups (flag_uneven).  Each lane takes
+// four of eight records at a time.  FP32 between wrapped positions decides outside a band
+// around rcl^2 (a component: 1 2^-24 of the largest coordinate L for the rounding of either
+// position and for their difference, reach for that of the shift, 1 + reach for the sum), the
+// exact FP64 test inside it; lattice images come with the records unless the image's atoms are
+// far.
 // Bound by the chain of a lane's record loads: 3 images of 55,295 LJ atoms written five cells
 // away 255 us a build (570 us with one lane an atom and FP64 tests of gathered positions, one
 // at a time), a step that builds 7 images of 102,399 atoms in a cell one lattice constant

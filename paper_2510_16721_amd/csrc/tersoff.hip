@@ -321,8 +321,10 @@ __device__ void ts_atom_regs(const TersoffT<T>& P, const vec4_t<T> (&bond)[MAXB]
 // lane walking them through memory held its whole wave, and in a small band the launch: a
 // chain of cnt^2 loads (a 511-atom vacancy hop, whose hopping atom has such a shell:
 // 36 us a launch, 14 us this way; 98,304 atoms, 22 images on their way to diamond: a step
-// 505 -> 406 us).  i, cnt: the group's atom and its bonds (0: idle group); most: the largest
-// cnt of the wave.
+// 505 -> 406 us).  G is the least of 8, 16, 32 and 64 that holds the atom's bonds: carbon on an
+// FCC lattice (12 bonds an atom), 4,000 atoms x 5 images, a step 192 us by one lane, 347 by 64,
+// 143 by 16; with 18 bonds 339, 468 and (32 lanes) 282 us.  i, cnt: the group's atom and its
+// bonds (0: idle group); most: the largest cnt of the wave.
 template <typename T, int G>
 __device__ void ts_atom_group(const TersoffT<T>& P, const vec4_t<T>& de, int cid, gmem<P3<T>>* Pout, size_t N, int i,
                               int cnt, int most, double* acc)
@@ -514,7 +516,9 @@ __device__ void ts_many_bonds(const BandDev& b, int slot, int tile)
     const int nb = i < b.N ? b.ncnt[size_t(slot) * N + i] : 0;
     double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     ts_crowded<T, 8>(P, __ballot(nb > TS_LDS_BONDS && nb <= 8), nb, i, dv, bcid, gp(Praw), N, acc);
-    ts_crowded<T, 64>(P, __ballot(nb > 8 && nb <= 64), nb, i, dv, bcid, gp(Praw), N, acc);
+    ts_crowded<T, 16>(P, __ballot(nb > 8 && nb <= 16), nb, i, dv, bcid, gp(Praw), N, acc);
+    ts_crowded<T, 32>(P, __ballot(nb > 16 && nb <= 32), nb, i, dv, bcid, gp(Praw), N, acc);
+    ts_crowded<T, 64>(P, __ballot(nb > 32 && nb <= 64), nb, i, dv, bcid, gp(Praw), N, acc);
     if (nb > 64)
         ts_atom_generic<T>(P, dv, reinterpret_cast<vec2_t<T>*>(b.bo) + size_t(slot) * b.cap * N, bcid, Praw, N, i, nb,
                            acc);
