@@ -109,7 +109,13 @@ bool make_layout(const cfneb_params* p, int64_t n_atoms, int max_images, Layout*
 // Lanes sharing an atom in the LJ force kernel, a property of the band: from the tables
 // that tune_lanes.py measures (bands by atoms x moving images, a count that also does for a
 // full batch; relaxations by atoms, the fastest alone), or CFNEB_LJ_LANES.
-int lj_lanes_for(long long atoms, int images, bool fp64, bool relax)
+// The tables are of the cutoff 2.5 with the skin 0.3, 24 fours of candidates an atom in a
+// crystal (about one atom a sigma^3).  A shorter cutoff has fewer, and lanes without a few
+// rounds of them cost a full batch and gain a band alone nothing: 2,047 atoms x 3 moving images
+// with 1, 2, 4 and 8 lanes, cutoff 1.3 alone 63.5, 63.2, 62.8, 62.4 us a step, 128 of them 150,
+// 171, 199, 235; cutoff 1.8 66, 64, 62, 62 and 181, 203, 223, 282; cutoff 2.1 71, 68, 65, 64 and
+// 226, 244, 274, 313.  So a band's lanes have 2.75 fours each, in the mean, or are one.
+int lj_lanes_for(long long atoms, int images, double reach, bool fp64, bool relax)
 {
     const char* v = std::getenv("CFNEB_LJ_LANES");
     if (v) {
@@ -120,7 +126,10 @@ int lj_lanes_for(long long atoms, int images, bool fp64, bool relax)
     const LjLanesEntry* e = relax ? (fp64 ? kLjLanesRelaxFp64 : kLjLanesRelax) : fp64 ? kLjLanesFp64 : kLjLanesTable;
     const long long work = atoms * (images - 2);
     while (work > e->max_atom_images) ++e;
-    return e->lanes;
+    int lanes = e->lanes;
+    const double fours = 1.126 * reach * reach * reach;  // reach: list cutoff over sigma
+    while (!relax && lanes > 1 && 2.75 * lanes > fours) lanes /= 2;
+    return lanes;
 }
 
 // Grids of a band table, bounded by the most items its bands can hold.
@@ -253,7 +262,7 @@ void fill_dev(cfneb_band* b, void* ws, const double* h0, int relax)
     d.rcl = d.rc + d.skin;
     d.rcl2 = d.rcl * d.rcl;
     d.lj_eps = p->lj_eps;
-    d.lj_lanes = lj_lanes_for(L.N, p->n_images, d.fp64 != 0, relax != 0);
+    d.lj_lanes = lj_lanes_for(L.N, p->n_images, d.rcl / p->lj_sigma, d.fp64 != 0, relax != 0);
     d.lj_tile = std::max(CFNEB_TILE / d.lj_lanes, lj_least_tile(L.N));
     d.ntF = p->potential == CFNEB_LJ ? (L.N + d.lj_tile - 1) / d.lj_tile : L.ntA;
     d.lj_sig2 = p->lj_sigma * p->lj_sigma;
