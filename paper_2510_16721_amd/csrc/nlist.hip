@@ -27,8 +27,9 @@
 //                  image, 4096 counts per pass, coalesced); zeroes the counts
 //   k_bin_scatter  (rebuilds) atom -> bin-ordered 16-byte record (BinAtom)
 //   k_bin_sort     (rebuilds) sort each bin by atom id, so lists are deterministic
-//   k_cand         (rebuilds) pairs within rcl by groups of bins, a wave to a group; the
-//                  packed candidate lists; R_ref = R
+//   k_cand         (rebuilds) pairs within rcl by groups of bins, a wave to a group (narrow
+//                  cells, far images and crowded shares: two lanes to an atom); the packed
+//                  candidate lists; R_ref = R
 //   k_filter       (host readouts only: the force kernels test their candidates
 //                  themselves) exact test of every candidate, packed entry-major
 //                  neighbour lists (entry e of atom i at [e][i])
